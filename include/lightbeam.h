@@ -151,9 +151,11 @@ typedef struct lb_stats {
   int64_t probe_lines;  /* 64-B hash-table lines read by the LM lookups (n-gram
                            tables and the explicit-continuation index)           */
   int64_t lm_lookups;   /* n-gram lookups done: one per distinct (context, word)
-                           among a stream-frame's queries, except homophones of
-                           heavy nodes that the continuation index shows to back
-                           off to their unigram (scored without a lookup)       */
+                           among the queries of a stream-frame that one wavefront
+                           scores (up to 4 completed words, more where many are
+                           completed), except homophones of heavy nodes that the
+                           continuation index shows to back off to their unigram
+                           (scored without a lookup)                            */
   int64_t launches[8];  /* kernel launches: [0] decode (all frames of a call), [1]
                            output, [2] external-fusion select, [3] export, [4]
                            apply, [5] stream reset, [6..7] unused                */
@@ -162,12 +164,14 @@ typedef struct lb_stats {
   int64_t index_lines;  /* the part of probe_lines read from the explicit-
                            continuation index                                     */
   int64_t phase_cycles[8]; /* with LB_PROFILE_PHASES: clock cycles of the decode
-                           launches' workgroups, summed over streams, by phase:
-                           [0] recombination and stay scores, [1] top-K and theta,
-                           [2] new beam, [3] grouping of the n-gram queries and
-                           the continuation index, [4] n-gram lookups, [5]
-                           ranking of the completed words (top-o, lambda) and
-                           history nodes, [6] fusion and the rest of the frame,
+                           launches' workgroups, summed over streams, by phase,
+                           as a wavefront that scores words sees them: [0] the
+                           part of the next frame's recombination that the
+                           scoring does not cover, and the bin range, [1] top-K
+                           and theta, [2] new beam, [3] grouping of the n-gram
+                           queries, [4] continuation index and n-gram lookups,
+                           [5] ranking of the completed words (top-o, lambda) and
+                           history nodes, [6] fusion (0 without fusion frames),
                            [7] beam load / write-back / output                  */
 } lb_stats;
 

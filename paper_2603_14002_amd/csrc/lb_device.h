@@ -57,11 +57,13 @@ constexpr uint32_t kFlagBuildDup = 32u;
 constexpr uint32_t kFlagBuildFull = 64u;
 constexpr uint32_t kFlagLength = 128u;  // a decode call's length outside 0..frames (clamped)
 
-// phases of a decode frame timed by the phase counters: recombination and stay
-// scores, top-K selection, new beam, grouping of the n-gram queries (with the
-// continuation index), the n-gram lookups, ranking of the completed words and
-// history nodes, the rest of the frame (fusion, trie-node store, next row);
-// kPhOther: beam load, write-back and output outside the frame loop
+// phases of a decode frame timed by the phase counters, as the first wavefront
+// that scores completed words sees them: what the next frame's recombination
+// (other wavefronts, at the same time) takes longer than the scoring, and the
+// bin range; top-K selection; new beam; grouping of the n-gram queries; the
+// lookups (continuation index and n-grams); ranking of the completed words and
+// history nodes; fusion; kPhOther: beam load, write-back and output outside the
+// frame loop
 enum { kPhRecomb = 0, kPhTopK = 1, kPhNewBeam = 2, kPhGroup = 3, kPhLookup = 4, kPhRank = 5, kPhFusion = 6,
        kPhOther = 7, kPhases = 8 };
 constexpr uint32_t kOptPhaseTimers = 1u;  // k_decode option: per-phase clock cycles

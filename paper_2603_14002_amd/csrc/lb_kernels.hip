@@ -40,6 +40,14 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Orders LDS accesses among the lanes of a wavefront (the hardware runs them in
+// order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Cross-lane moves inside rows of 16 lanes (DPP): lane i reads lane i^1
 // (quad_perm [1,0,3,2]), lane i^2 (quad_perm [2,3,0,1]), the mirror lane in
 // its half-row (7-i) and in its row (15-i).  Applying an associative,
@@ -52,6 +60,12 @@ constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirr
 template <int CTRL>
 __device__ __forceinline__ int dpp_i32(int x, int ident) {
   return __builtin_amdgcn_update_dpp(ident, x, CTRL, 0xF, 0xF, false);
+}
+
+// The value of lane L of the lane's quad.
+template <int L>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), L * 0x55, 0xF, 0xF, true));
 }
 
 template <int CTRL>
@@ -106,6 +120,18 @@ __device__ __forceinline__ void argmax_step(double* L, int* q) {
   const bool take = oL > *L || (oL == *L && oq < *q);
   *L = take ? oL : *L;
   *q = take ? oq : *q;
+}
+
+// The same with a payload that travels with the winner.
+template <int CTRL>
+__device__ __forceinline__ void argmax_step(double* L, int* q, int* s) {
+  const double oL = dpp_f64<CTRL>(*L, -HUGE_VAL);
+  const int oq = dpp_i32<CTRL>(*q, 0x7FFFFFFF);
+  const int os = dpp_i32<CTRL>(*s, 0);
+  const bool take = oL > *L || (oL == *L && oq < *q);
+  *L = take ? oL : *L;
+  *q = take ? oq : *q;
+  *s = take ? os : *s;
 }
 
 // Wavefront arg-max of (L desc, q asc), in every lane.
@@ -407,9 +433,7 @@ __device__ __forceinline__ bool resolve(const Table& t, uint64_t key, uint64_t b
 }
 
 // log10 P(w | the last three words of history ctx) by Katz backoff over the
-// hashed tables (Eq. (1), App. E.3), and the n-gram state after w.  The three
-// bucket lines (orders 2, 3, 4) and the unigram are loaded together, then
-// resolved; `lines` counts the bucket lines read.
+// hashed tables (Eq. (1), App. E.3), and the n-gram state after w.
 struct LmResult {
   double lp;
   QState st;
@@ -434,49 +458,38 @@ __device__ __forceinline__ Ctx ctx_of(const HistNode& h) {
   return c;
 }
 
-__device__ __forceinline__ LmResult lm_lookup(const DevState& S, int32_t w, const Ctx& ctx, uint32_t* lines) {
-  const uint64_t k2 = (static_cast<uint64_t>(static_cast<uint32_t>(ctx.word)) << 32) | static_cast<uint32_t>(w);
-  const uint64_t k3 = (static_cast<uint64_t>(ctx.c2) << 32) | static_cast<uint32_t>(w);
-  const uint64_t k4 = (static_cast<uint64_t>(ctx.c3) << 32) | static_cast<uint32_t>(w);
-  const bool has3 = ctx.c2 != kNone;
-  const bool has4 = ctx.c3 != kNone;
-  const uint64_t b2 = bucket_of(k2, S.t2.nbuckets);
-  const uint64_t b3 = has3 ? bucket_of(k3, S.t3.nbuckets) : 0;
-  const uint64_t b4 = has4 ? bucket_of(k4, S.t4.nbuckets) : 0;
-  const Bucket q2 = load_bucket(S.t2, b2);
-  const Bucket q3 = has3 ? load_bucket(S.t3, b3) : Bucket{};
-  const Bucket q4 = has4 ? load_bucket(S.t4, b4) : Bucket{};
-  const Unigram u = S.uni[w];
-  *lines += 1u + (has3 ? 1u : 0u) + (has4 ? 1u : 0u);
-  uint32_t s2 = kNone, s3 = kNone, s4 = kNone;
-  uint32_t z2 = 0, y2 = 0, z3 = 0, y3 = 0, z4 = 0, y4 = 0;
-  const bool f2 = resolve(S.t2, k2, b2, q2, &s2, &z2, &y2, lines);
-  const bool f3 = has3 && resolve(S.t3, k3, b3, q3, &s3, &z3, &y3, lines);
-  const bool f4 = has4 && resolve(S.t4, k4, b4, q4, &s4, &z4, &y4, lines);
-  const float p2 = __uint_as_float(z2), bb2 = __uint_as_float(y2), p3 = __uint_as_float(z3),
-              bb3 = __uint_as_float(y3), p4 = __uint_as_float(z4);
+// Result of one probe: the slot index and the slot's two values (kNone, 0 and 0
+// where the key is absent).
+struct Hit {
+  uint32_t slot, z, y;
+};
+
+// log10 P(w | ctx) and the state after w from the probes of orders 2, 3 and 4.
+__device__ __forceinline__ LmResult lm_result(const Hit& h2, const Hit& h3, const Hit& h4, float bo1, float bo2,
+                                              float bo3, int32_t w, float logp, float bo) {
+  const bool f2 = h2.slot != kNone, f3 = h3.slot != kNone, f4 = h4.slot != kNone;
   // log10 P(w | context) by backoff, innermost order first
   double lp;
   if (f4) {
-    lp = static_cast<double>(p4);
+    lp = static_cast<double>(__uint_as_float(h4.z));
   } else {
     double l3;
     if (f3) {
-      l3 = static_cast<double>(p3);
+      l3 = static_cast<double>(__uint_as_float(h3.z));
     } else {
-      const double l2 = f2 ? static_cast<double>(p2) : static_cast<double>(ctx.bo1) + static_cast<double>(u.logp);
-      l3 = static_cast<double>(ctx.bo2) + l2;
+      const double l2 = f2 ? static_cast<double>(__uint_as_float(h2.z)) : static_cast<double>(bo1) + static_cast<double>(logp);
+      l3 = static_cast<double>(bo2) + l2;
     }
-    lp = static_cast<double>(ctx.bo3) + l3;
+    lp = static_cast<double>(bo3) + l3;
   }
   LmResult r;
   r.lp = lp;
-  r.st.c2 = f2 ? s2 : kNone;
-  r.st.c3 = f3 ? s3 : kNone;
-  r.st.bo2 = f2 ? bb2 : 0.0f;
-  r.st.bo3 = f3 ? bb3 : 0.0f;
+  r.st.c2 = h2.slot;
+  r.st.c3 = h3.slot;
+  r.st.bo2 = f2 ? __uint_as_float(h2.y) : 0.0f;
+  r.st.bo3 = f3 ? __uint_as_float(h3.y) : 0.0f;
   r.st.w = w;
-  r.st.bo1 = u.bo;
+  r.st.bo1 = bo;
   return r;
 }
 
@@ -490,40 +503,21 @@ __device__ __forceinline__ unsigned long long group_key(const Ctx& ctx, uint32_t
   return (tag << 62) | (id << 30) | woff;
 }
 
-// The homophones of the node at word offset `woff` that have an explicit
-// n-gram with context `ctx`, from the explicit-continuation index of orders 2,
-// 3 and 4 (contexts: the last word, the 2-word slot, the 3-word slot).  The
-// first buckets of the three probes are loaded together.  Order n's result is
-// hit[n-2] = {a, count}: the index is `a` itself when count == 1, else
-// lists[a..a+count).
-struct PresHit {
-  uint32_t a, n;
-};
-
-__device__ __forceinline__ void pres_lookup(const DevState& S, const Ctx& ctx, uint32_t woff, PresHit* hit,
-                                            uint32_t* lines) {
-  const uint64_t k2 = (static_cast<uint64_t>(static_cast<uint32_t>(ctx.word)) << 32) | woff;
-  const uint64_t k3 = (static_cast<uint64_t>(ctx.c2) << 32) | woff;
-  const uint64_t k4 = (static_cast<uint64_t>(ctx.c3) << 32) | woff;
-  const bool has3 = ctx.c2 != kNone;
-  const bool has4 = ctx.c3 != kNone;
-  const uint64_t b2 = bucket_of(k2, S.p2.nbuckets);
-  const uint64_t b3 = has3 ? bucket_of(k3, S.p3.nbuckets) : 0;
-  const uint64_t b4 = has4 ? bucket_of(k4, S.p4.nbuckets) : 0;
-  const Bucket q2 = load_bucket(S.p2, b2);
-  const Bucket q3 = has3 ? load_bucket(S.p3, b3) : Bucket{};
-  const Bucket q4 = has4 ? load_bucket(S.p4, b4) : Bucket{};
-  *lines += 1u + (has3 ? 1u : 0u) + (has4 ? 1u : 0u);
-  uint32_t slot;
-  hit[0] = PresHit{0, 0};
-  hit[1] = PresHit{0, 0};
-  hit[2] = PresHit{0, 0};
-  resolve(S.p2, k2, b2, q2, &slot, &hit[0].a, &hit[0].n, lines);
-  if (has3) resolve(S.p3, k3, b3, q3, &slot, &hit[1].a, &hit[1].n, lines);
-  if (has4) resolve(S.p4, k4, b4, q4, &slot, &hit[2].a, &hit[2].n, lines);
-}
-
 // ------------------------------------------------------------------ decoding loop
+
+// A wavefront that scores completed words: words and lookups per turn, lookup
+// results kept in LDS (further ones go to the stream's scratch), homophones up
+// to which a fully looked-up group is ranked by one lane.
+constexpr int kWaveWords = 64 / kMaxSub;
+constexpr int kWaveTasks = 16;
+constexpr int kLmRes = 64;
+constexpr uint32_t kLaneMaxH = 16;
+struct LmWave {
+  double lp[kLmRes];
+  QState st[kLmRes];
+  uint8_t owner[kWaveTasks];  // the group (its first lane) of each task
+};
+static_assert(sizeof(LmWave) % 8 == 0, "wavefront scratch alignment");
 
 // A stream's hypotheses in LDS (structure of arrays); the fields of each
 // hypothesis' trie node travel with it.
@@ -557,18 +551,26 @@ __device__ __forceinline__ void emit_output(const DevParams& P, const DevState& 
 //     exact rank inside the boundary bin), beam update, trie-state advance;
 //     hypothesis i is owned by LPB consecutive lanes: lane s of it handles the
 //     extensions v = 1+s, 1+s+LPB, ... and lane 0 also the merged stay;
-//   * Eq. (1) for the hypotheses that completed a word (in batches of NEB
-//     words): the (word, sub-beam) pairs are grouped by (n-gram context, trie
-//     node); each group is looked up once per homophone, or, for a node with
-//     many homophones, only for those the explicit-continuation index lists
-//     (the others back off to their unigrams); the lookups are spread over all
-//     threads; each word's top-o (one thread per word, or a wavefront for a
-//     word with a large fully looked-up group) survive lambda pruning and
-//     receive word-history nodes;
+//   * Eq. (1) for the hypotheses that completed a word, by wavefronts of their
+//     own (score_words): the (word, sub-beam) pairs are grouped by (n-gram
+//     context, trie node); each group is looked up once per homophone, or, for
+//     a node with many homophones, only for those the explicit-continuation
+//     index lists (the others back off to their unigrams); each word's top-o
+//     (four lanes per word, or a wavefront for a word with a large fully
+//     looked-up group) survive lambda pruning and receive word-history nodes.
+//     Meanwhile the wavefronts that hold the hypotheses recombine the next
+//     frame's (one thread per hypothesis), which needs no word-level score.
+//     Before, the whole workgroup went through Eq. (1) in six barrier-separated
+//     steps and then through the recombination: 512 x 500 frames at K = 256
+//     9.05 -> 7.39 ms, 256 x 500 at K = 64 5.21 -> 4.17, 64 x 200 at K = 32
+//     2.02 -> 1.60, 100 x 333 at K = 100 with four sub-beams 4.15 -> 3.01;
 //   * Eq. (2) with the synthetic scorer on fusion frames.
 // After the last frame the beam goes back to global memory, and, when out_hyps
 // is given, the workgroup also writes the stream's output (emit_output; out_fin:
 // the end of the utterance).
+// Barriers per frame: the bin range, the histogram, the bin search, the boundary
+// bin's list, the block scan, the gather, the new hypotheses (two when in
+// place), and the one that joins Eq. (1) and the next recombination.
 // WPE: wavefronts per SIMD the register allocation aims for (four workgroups
 // of 256 threads per CU need 4).  DB: the hypotheses are double-buffered in
 // LDS; otherwise one buffer is rewritten in place (every source entry is read
@@ -609,18 +611,27 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   static_assert(NC + 2 < 64, "a lane's candidates (its slots, the stay and the repeat) fit the sets sel_bits and bnd");
   // the candidate sets of a lane: 32 bits where its positions fit
   using CandSet = typename std::conditional<(NC + 2 <= 32), uint32_t, uint64_t>::type;
-  constexpr int NPM = KMAX * kMaxSub;  // (completed word, sub-beam) pairs per frame, at most
-  constexpr int NPL = NPM < 256 ? NPM : 256;  // pairs grouped at once
-  constexpr int NEB = NPL / kMaxSub;          // completed words per batch
+  // the wavefronts that hold the hypotheses (one thread each), and those that
+  // score completed words meanwhile: the others, as many as a beam can fill
+  // (every wavefront, before its other work, where none is left)
+  constexpr int RW = (KMAX + 63) / 64;
+  constexpr bool kSplit = NW > RW;
+  constexpr int kWordWaves = (KMAX + kWaveWords - 1) / kWaveWords;
+  constexpr int LMW = !kSplit ? NW : (NW - RW < kWordWaves ? NW - RW : kWordWaves);
   // score bins of the top-K selection: 1024 at K = 256; 512 for the smaller
   // beams' fewer candidates (c5: 25.69 against 25.83 ms with 1024; c4 9.91
   // against 9.80 with 512)
   constexpr int kBinBits = KMAX >= 256 ? 10 : 9;
   constexpr int kBins = 1 << kBinBits;
   constexpr int SEL_BYTES = kBins * 4 + kBoundaryCap * 16;
-  constexpr int LM_BYTES = 64 * NPL + 16;
-  constexpr int UNI_BYTES = SEL_BYTES > LM_BYTES ? SEL_BYTES : LM_BYTES;
-  static_assert(20 * KMAX <= SEL_BYTES, "fusion sort scratch");
+  constexpr int LM_BYTES = LMW * static_cast<int>(sizeof(LmWave));
+  // in place: the new hypotheses' sub-beams on their way; K >= 128: the top F
+  constexpr int STAGE_BYTES = DB ? 0 : 12 * KMAX * kMaxSub;
+  constexpr int FUSE_BYTES = KMAX >= 128 ? 4 * kBins + 24 * KMAX : 20 * KMAX;
+  constexpr int MAX1 = SEL_BYTES > LM_BYTES ? SEL_BYTES : LM_BYTES;
+  constexpr int MAX2 = STAGE_BYTES > FUSE_BYTES ? STAGE_BYTES : FUSE_BYTES;
+  constexpr int UNI_BYTES = MAX1 > MAX2 ? MAX1 : MAX2;
+  static_assert(20 * KMAX <= SEL_BYTES, "output sort scratch");
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -629,40 +640,44 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   const int tend = len < tau1 ? len : tau1;
 
   __shared__ BeamLds<KMAX> sBeam[DB ? 2 : 1];
-  __shared__ double sD[64];  // classes 0..40; 41..63 are zero (slots past the separator)
-  __shared__ double sDmax;   // the largest of sD[1..40]
-  __shared__ double sAb2[KMAX], sAnb2[KMAX], sPt2[KMAX], sStay[KMAX];
-  __shared__ uint64_t sMask[KMAX];
+  // this frame's row and the next one's: classes 0..40; 41..63 are zero (slots past the separator)
+  __shared__ double sD[2][64];
+  __shared__ double sDmax[2];  // the largest of classes 1..40
+  __shared__ double sAb2[KMAX], sAnb2[KMAX], sPt2[KMAX];
+  __shared__ uint64_t sCut[KMAX];  // symbols whose extension went to a live hypothesis' stay
   // the prefix keys of the frame's hypotheses: inserted when the hypotheses
   // are written (in the previous frame, or when the beam is loaded), cleared
   // once this frame's parent lookups are done (the frame's later barriers
   // separate the clear from the next inserts)
   __shared__ unsigned long long sHKey[HS];
   __shared__ uint8_t sHIdx[HS];  // the slot's hypothesis (KMAX <= 256)
-  // top-K selection scratch; the LM step and the fusion sort reuse it
+  // top-K selection scratch; the LM step, the fusion and the output reuse it
   __shared__ __align__(16) unsigned char sSel[UNI_BYTES];
   __shared__ double sLvHi[kMaxLevels], sLvInv[kMaxLevels];
   __shared__ int32_t sLvBeta[kMaxLevels], sLvShift[kMaxLevels];
   __shared__ uint32_t sSelSrc[KMAX];
-  // hypotheses that completed a word this frame
+  // hypotheses that completed a word this frame: those of wavefront w from 64 w on
   __shared__ uint32_t sEvBeam[KMAX], sEvWoff[KMAX], sEvH[KMAX];
-  __shared__ int32_t sNG, sHeavy, sNLarge;
-  __shared__ int32_t sLarge[KMAX];  // completed words ranked by a whole wavefront
+  __shared__ int32_t sEvCnt[RW];
   __shared__ double sRed[2 * NW], sRedB[3 * NW];
-  __shared__ int32_t sScan[NW], sScanB[NW], sScanC[NW], sScanD[NW];
+  __shared__ int32_t sScan[NW], sScanB[NW], sScanD[NW];
   __shared__ int32_t sBucket, sAbove, sBucketCnt, sBCount, sAthr, sNBinned;
   // counters: probed lines, completed words, LM queries, index lines (summed over
   // the threads at the end), expansions, fused hypotheses, lookups (added by
   // thread 0 as they occur: kept here, not in every thread's registers)
   __shared__ unsigned long long sCnt[7];
-  // phase cycles of thread 0 (kPh*), and the last timestamp
+  // phase cycles of one thread (kPh*), and the last timestamp
   __shared__ unsigned long long sPhase[kPhases + 1];
+  // tables of orders 2..4 and of the continuation index
+  __shared__ NgramTable sTab[6];
   // the log-sum-exp's series coefficients (log1p_unit), read from LDS
   __shared__ double sAtanh[kAtanhTerms];
   const bool timing = (opts & kOptPhaseTimers) != 0;
-  // closes the current phase as phase k (taken after the barrier that ends it)
+  // closes the current phase as phase k, by a thread of the first wavefront that
+  // scores words (taken after the barrier that ends the phase, or, inside Eq.
+  // (1), where that wavefront is done with it)
   auto mark = [&](int k) {
-    if (timing && threadIdx.x == 0) {
+    if (timing && threadIdx.x == (kSplit ? 64 * RW : 0)) {
       const unsigned long long now = __builtin_amdgcn_s_memtime();
       sPhase[k] += now - sPhase[kPhases];
       sPhase[kPhases] = now;
@@ -672,11 +687,10 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   uint32_t* const sHisto = reinterpret_cast<uint32_t*>(sSel);
   double* const sBScore = reinterpret_cast<double*>(sSel + kBins * 4);
   uint64_t* const sBKey = reinterpret_cast<uint64_t*>(sSel + kBins * 4 + kBoundaryCap * 8);
-  // write-back staging of the sub-beams (one-buffer instances), past the
-  // grouping keys that the write-back clears
-  double* const sStL = reinterpret_cast<double*>(sSel + 8 * NPL);
+  // write-back staging of the sub-beams (one-buffer instances)
+  double* const sStL = reinterpret_cast<double*>(sSel);
   uint32_t* const sStH = reinterpret_cast<uint32_t*>(sStL + KMAX * kMaxSub);
-  static_assert(DB || 8 * NPL + 12 * KMAX * kMaxSub <= UNI_BYTES, "write-back staging fits the shared scratch");
+  LmWave* const sLm = reinterpret_cast<LmWave*>(sSel);
   // the output (when this launch writes it) sorts in the shared scratch
   auto output = [&](const DevParams& Pr, const DevState& Sr) {
     emit_output<BLOCK, KMAX>(Pr, Sr, b, lengths, Tc, out_fin, out_hyps, out_scores, reinterpret_cast<double*>(sSel),
@@ -720,6 +734,13 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     B0.woff[tid] = tn.word_off;
   }
   if (tid < 7) sCnt[tid] = 0;
+  if (tid < 6) {
+    // (one layout for both kinds of table)
+    const NgramTable& t = tid == 0 ? S.t2 : (tid == 1 ? S.t3 : S.t4);
+    const PresTable& p = tid == 3 ? S.p2 : (tid == 4 ? S.p3 : S.p4);
+    sTab[tid].slots = tid < 3 ? t.slots : reinterpret_cast<Slot*>(p.slots);
+    sTab[tid].nbuckets = tid < 3 ? t.nbuckets : p.nbuckets;
+  }
   if (tid < kAtanhTerms) sAtanh[tid] = 1.0 / (2 * tid + 3);
   if (timing && tid == 0) {
     for (int k = 0; k < kPhases; ++k) sPhase[k] = 0;
@@ -740,7 +761,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       s = (s + 1) & (HS - 1);
     }
   };
-  uint32_t lines = 0, plines = 0, c_words = 0;  // per thread
+  uint32_t lines = 0, plines = 0, c_words = 0, c_look = 0;  // per thread
   uint64_t c_queries = 0;
   const ScratchLayout slay = scratch_layout(gridDim.x, S.scap, P.K);
   double* const scrL = (scratch ? reinterpret_cast<double*>(scratch) : S.scrL) + static_cast<size_t>(b) * S.scap;
@@ -748,9 +769,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       (scratch ? reinterpret_cast<QState*>(scratch + slay.off_state) : S.scrS) + static_cast<size_t>(b) * S.scap;
   uint32_t* const scrE = (scratch ? reinterpret_cast<uint32_t*>(scratch + slay.off_explicit) : S.scrE) +
                          static_cast<size_t>(b) * P.K * kMaxSub * kMaxExplicit;
-  // D = alpha * log-probs of a frame into sD, by wavefront 0 (every lane):
-  // raw scores are first normalised by a log-softmax over the 41 classes
-  auto set_row = [&](const DevParams& Pr, float xin) {
+  // D = alpha * log-probs of a frame into row q of sD, by one wavefront (every
+  // lane): raw scores are first normalised by a log-softmax over the 41 classes
+  auto set_row = [&](const DevParams& Pr, int q, float xin) {
     double x = lane < kClasses ? static_cast<double>(xin) : kNegInf;
     if (Pr.raw_input) {
       double m = x, unused = x;
@@ -759,23 +780,551 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       x = (x - m) - log(sum);
     }
     const double dv = lane < kClasses ? Pr.alpha * x : 0.0;
-    sD[lane] = dv;
+    sD[q][lane] = dv;
     const double dm = wave_max(lane >= 1 && lane < kClasses ? dv : kNegInf);
-    if (lane == 0) sDmax = dm;
+    if (lane == 0) sDmax[q] = dm;
   };
-  // the first frame's row now; each frame loads the next frame's row early and
-  // writes it to sD after the frame's last global wait
+  // the first frame's row now; in each frame the last wavefront loads the next
+  // frame's row early and sets it while the first one searches the top-K's bins
+  int row = 0;
   if (wave == 0)
-    set_row(P, lane < kClasses ? logits[(static_cast<size_t>(b) * Tc + tau0) * kClasses + lane] : 0.0f);
+    set_row(P, 0, lane < kClasses ? logits[(static_cast<size_t>(b) * Tc + tau0) * kClasses + lane] : 0.0f);
   float dnext = 0.0f;
   lds_barrier();
-  // the loaded hypotheses' keys and trie masks for the first frame
+  // the loaded hypotheses' keys for the first frame
   if (tid < n) {
     insert_key(sBeam[0].key[tid], tid);
-    sMask[tid] = sBeam[0].tmask[tid];
+    sCut[tid] = 0;
   }
   lds_barrier();
   mark(kPhOther);
+
+  // ---- recombination of a frame's hypotheses (buffer H, log-probs D): a
+  // hypothesis whose parent prefix is also live receives the parent's extension
+  // by its last symbol; that extension is removed from the parent's fan-out
+  // (sCut).  Stay candidates: blank-stay, repeat-stay, merged parent extension.
+  // Reads nothing that Eq. (1) writes (it adds the word-level scores later), so
+  // the wavefronts that hold the hypotheses run it while the others score the
+  // words that the frame before completed.
+  auto recombine = [&](const DevParams& Pr, BeamLds<KMAX>& H, const double* D, int nh, int tid) {
+    if (tid < nh) {
+      const uint64_t pkey = H.pkey[tid];
+      const int last = H.meta[tid] & 0xFF;
+      int par = -1;
+      if (pkey != kNoParent) {
+        uint32_t s = static_cast<uint32_t>(pkey) & (HS - 1);
+        for (int probes = 0; probes < HS; ++probes) {
+          const unsigned long long k = sHKey[s];
+          if (k == kEmptyKey) break;
+          if (k == pkey) {
+            par = static_cast<int>(sHIdx[s]);
+            break;
+          }
+          s = (s + 1) & (HS - 1);
+        }
+        if (par >= 0) atomicOr(reinterpret_cast<unsigned long long*>(&sCut[par]), 1ull << last);
+      }
+      const double ab2 = H.pt[tid] + D[0];
+      const double rep = last ? H.anb[tid] + D[last] : kNegInf;
+      double ext = kNegInf;
+      if (par >= 0) {
+        const double base = (last == static_cast<int>(H.meta[par] & 0xFF)) ? H.ab[par] : H.pt[par];
+        ext = (base + D[last]) + (last == kSep ? Pr.gamma : Pr.beta);
+      }
+      // anb2 = merge(rep, ext), then pt2 = merge(ab2, anb2); merge is
+      // log-sum-exp, or max for the best-alignment recombination
+      double x = rep, y = ext, anb2 = 0.0;
+#pragma unroll 1
+      for (int pass = 0; pass < 2; ++pass) {
+        const double l = Pr.merge_max ? fmax(x, y) : lse2(x, y, [&](int k) { return sAtanh[k]; });
+        if (pass == 0) {
+          anb2 = l;
+          x = ab2;
+          y = l;
+        } else {
+          y = l;
+        }
+      }
+      sAb2[tid] = ab2;
+      sAnb2[tid] = anb2;
+      sPt2[tid] = y;
+    }
+  };
+
+  // ---- Eq. (1) for the words that a frame completed (events 0..nev-1 of buffer
+  // H), by one wavefront for 4 to kWaveWords words at a time: lane 4 el + j holds
+  // sub-beam j of word el.  No barrier: each of the nw wavefronts that score
+  // takes its own words.
+  //   * the pairs (word, sub-beam) of equal group -- n-gram context and
+  //     completed-word node -- share the lookups of the first of them;
+  //   * round 1: the lookups of the groups with few homophones, and one task
+  //     per heavy group for the continuation index; round 2: the heavy groups'
+  //     listed homophones (or all, if the list is long).  A task takes four
+  //     lanes, one per order and one for the unigram, so that a lane holds one
+  //     64-B bucket (three of them would not fit the registers);
+  //   * each lane ranks its sub-beam's candidates, the four lanes of a word
+  //     merge their top-o, and lane k of them writes the k-th history node.
+  // Bound by the latency of its dependent reads (history node, hash-table
+  // lines, unigram order), each made by all lanes at once.
+  auto score_words = [&](const DevParams& Pr, const DevState& Sr, BeamLds<KMAX>& H, int nev, int wv, int nw, int lane) {
+    LmWave& W = sLm[wv];
+    // words per turn: up to 4 words share a wavefront's lookups, more are spread
+    int per = (nev + nw - 1) / nw;
+    per = per < 4 ? 4 : (per > kWaveWords ? kWaveWords : per);
+#pragma unroll 1
+    for (int e0 = wv * per; e0 < nev; e0 += nw * per) {
+      const int j = lane & (kMaxSub - 1);
+      const int el = lane / kMaxSub;
+      const int e = e0 + el;
+      const bool word = el < per && e < nev;
+      uint32_t rr = 0, woff = 0, Hn = 0, ph = 0;
+      int nsub = 0;
+      double Lw = kNegInf;
+      Ctx ctx{};
+      int32_t w0 = 0, w1 = 0;
+      unsigned long long key = 0;
+      if (word) {
+        int k = e;
+#pragma unroll
+        for (int w = 0, left = e; w < RW; ++w) {
+          if (left >= 0 && left < sEvCnt[w]) k = 64 * w + left;
+          left -= sEvCnt[w];
+        }
+        rr = sEvBeam[k];
+        woff = sEvWoff[k];
+        Hn = sEvH[k];
+        nsub = (H.meta[rr] >> 8) & 0xFF;
+      }
+      const bool pair = word && j < nsub;
+      if (pair) {
+        ph = H.hist[rr * kMaxSub + j];
+        Lw = H.Lw[rr * kMaxSub + j];
+        ctx = ctx_of(Sr.arena[ph]);
+        w0 = Sr.trie_words[woff];
+        if (Hn > 1) w1 = Sr.trie_words[woff + 1];
+        key = group_key(ctx, woff);
+      }
+      // the groups: every pair's first lane of equal key
+      int lead = lane;
+      for (uint64_t left = __ballot(pair); left;) {
+        const int l = __builtin_ctzll(left);
+        const uint64_t kl =
+            static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key), l)) |
+            (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key >> 32), l))) << 32);
+        const bool same = pair && key == kl;
+        if (same) lead = l;
+        left &= ~__ballot(same);
+      }
+      const bool leader = pair && lead == lane;
+      const bool heavy = Hn >= Pr.heavy_min;
+      const uint64_t below = (1ull << lane) - 1ull;
+      // round 1's tasks and results (a heavy group's task has no result of its own)
+      int cnt = leader ? (heavy ? 1 : static_cast<int>(Hn)) : 0;
+      int incl = wave_scan_incl(cnt);
+      int pos = incl - cnt;
+      int U = __builtin_amdgcn_readlane(incl, 63);
+      const uint64_t hleads = __ballot(leader && heavy);
+      int roff = pos - __popcll(hleads & below);
+      int R = U - __popcll(hleads);
+      uint32_t gcnt = heavy ? kGroupHeavy : Hn;  // (leaders) lookups | kGroupHeavy
+      uint64_t gmask = 0;  // (leaders) heavy: bit h mod 64 of every listed homophone h
+      // a batch's results past those that LDS holds: the stream's scratch, from
+      // the words before it on
+      const size_t gbase = static_cast<size_t>(e0) * (static_cast<uint32_t>(Sr.scap) / static_cast<uint32_t>(Pr.K));
+      mark(kPhGroup);
+#pragma unroll 1
+      for (int round = 0; round < 2; ++round) {
+#pragma unroll 1
+        for (int c0 = 0; c0 < U; c0 += kWaveTasks) {
+          if (leader)
+            for (int q = pos > c0 ? pos : c0; q < pos + cnt && q < c0 + kWaveTasks; ++q)
+              W.owner[q - c0] = static_cast<uint8_t>(lane);
+          wave_sync();
+          const int o = lane & 3;  // this lane's part of the task: order o + 2, or the unigram
+          const bool task = c0 + lane / 4 < U;
+          const int own = task ? W.owner[lane / 4] : lane;
+          wave_sync();
+          const uint32_t k = static_cast<uint32_t>(c0 + lane / 4 - __shfl(pos, own, 64));
+          const uint32_t x1 = static_cast<uint32_t>(__shfl(ctx.word, own, 64));
+          const uint32_t x2 = static_cast<uint32_t>(__shfl(static_cast<int>(ctx.c2), own, 64));
+          const uint32_t x3 = static_cast<uint32_t>(__shfl(static_cast<int>(ctx.c3), own, 64));
+          const uint32_t gw = static_cast<uint32_t>(__shfl(static_cast<int>(woff), own, 64));
+          const uint32_t gH = static_cast<uint32_t>(__shfl(static_cast<int>(Hn), own, 64));
+          const uint32_t gc = static_cast<uint32_t>(__shfl(static_cast<int>(gcnt), own, 64));
+          const int a0 = __shfl(w0, own, 64), a1 = __shfl(w1, own, 64);
+          uint32_t* const E = scrE + static_cast<size_t>(e0 * kMaxSub + own) * kMaxExplicit;
+          const bool index = round == 0 && gH >= Pr.heavy_min;
+          uint32_t id = gw;
+          if (task && !index) {
+            uint32_t h = k;
+            if (round == 1 && (gc & kGroupHeavy)) h = E[k];
+            id = static_cast<uint32_t>(h == 0 ? a0 : (h == 1 ? a1 : Sr.trie_words[gw + h]));
+          }
+          Unigram un{0.0f, 0.0f};
+          if (task && !index && o == 3) un = Sr.uni[id];
+          Hit hit{kNone, 0, 0};
+          const uint32_t cid = o == 0 ? x1 : (o == 1 ? x2 : x3);
+          if (task && o < 3 && (o == 0 || cid != kNone)) {
+            const NgramTable tb = sTab[(index ? 3 : 0) + o];
+            const uint64_t pk = (static_cast<uint64_t>(cid) << 32) | id;
+            const uint64_t bk = bucket_of(pk, tb.nbuckets);
+            uint32_t nl = 1;
+            (void)resolve(tb, pk, bk, load_bucket(tb, bk), &hit.slot, &hit.z, &hit.y, &nl);
+            lines += index ? 0u : nl;
+            plines += index ? nl : 0u;
+          }
+          // the quad's findings in each of its lanes
+          const Hit h2{quad_bcast<0>(hit.slot), quad_bcast<0>(hit.z), quad_bcast<0>(hit.y)};
+          const Hit h3{quad_bcast<1>(hit.slot), quad_bcast<1>(hit.z), quad_bcast<1>(hit.y)};
+          const Hit h4{quad_bcast<2>(hit.slot), quad_bcast<2>(hit.z), quad_bcast<2>(hit.y)};
+          const float ulp = __uint_as_float(quad_bcast<3>(__float_as_uint(un.logp)));
+          const float ubo = __uint_as_float(quad_bcast<3>(__float_as_uint(un.bo)));
+          const float b1 = __shfl(ctx.bo1, own, 64), b2 = __shfl(ctx.bo2, own, 64), b3 = __shfl(ctx.bo3, own, 64);
+          const int gr = __shfl(roff, own, 64);
+          uint32_t tcnt = 0;
+          uint64_t tmask = 0;
+          if (task && o == 0) {
+            if (index) {
+              const uint32_t ne = h2.y + h3.y + h4.y;
+              tcnt = gH;
+              if (ne <= static_cast<uint32_t>(kMaxExplicit)) {
+                uint32_t nd = 0;
+                // each homophone once (it can be listed for several context
+                // orders); the list is read back only when its mask bit is set
+                auto add = [&](uint32_t x) {
+                  const uint64_t bit = 1ull << (x & 63u);
+                  bool seen = false;
+                  if (tmask & bit)
+                    for (uint32_t m = 0; m < nd; ++m) seen |= E[m] == x;
+                  if (!seen) {
+                    E[nd++] = x;
+                    tmask |= bit;
+                  }
+                };
+                auto add_list = [&](const Hit& h, const uint32_t* lists) {
+                  if (h.y == 1) {
+                    add(h.z);
+                  } else {
+                    for (uint32_t m = 0; m < h.y; ++m) add(lists[h.z + m]);
+                  }
+                };
+                add_list(h2, Sr.p2.lists);
+                add_list(h3, Sr.p3.lists);
+                add_list(h4, Sr.p4.lists);
+                tcnt = nd | kGroupHeavy;
+              }
+            } else {
+              const LmResult res = lm_result(h2, h3, h4, b1, b2, b3, static_cast<int32_t>(id), ulp, ubo);
+              const int u = gr + static_cast<int>(k);
+              if (u < kLmRes) {
+                W.lp[u] = res.lp;
+                W.st[u] = res.st;
+              } else {
+                scrL[gbase + u] = res.lp;
+                scrS[gbase + u] = res.st;
+              }
+            }
+          }
+          if (round == 0) {
+            // the index's findings back to the groups' leaders
+            const int at = pos - c0;
+            const bool mine = leader && heavy && at >= 0 && at < kWaveTasks;
+            const int src = (4 * at) & 63;
+            const uint32_t fc = static_cast<uint32_t>(__shfl(static_cast<int>(tcnt), src, 64));
+            const uint32_t fl = static_cast<uint32_t>(__shfl(static_cast<int>(tmask), src, 64));
+            const uint32_t fh = static_cast<uint32_t>(__shfl(static_cast<int>(tmask >> 32), src, 64));
+            if (mine) {
+              gcnt = fc;
+              gmask = fl | (static_cast<uint64_t>(fh) << 32);
+            }
+          }
+        }
+        if (lane == 0) c_look += static_cast<uint32_t>(round == 0 ? R : U);
+        if (round == 0) {
+          // round 2: the heavy groups' lookups
+          cnt = (leader && heavy) ? static_cast<int>(gcnt & ~kGroupHeavy) : 0;
+          incl = wave_scan_incl(cnt);
+          pos = incl - cnt;
+          U = __builtin_amdgcn_readlane(incl, 63);
+          if (leader && heavy) roff = R + pos;
+          if (U > 0) {  // the lists (global memory) are read by other lanes
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+          }
+        }
+      }
+      R += U;
+      if (R > kLmRes) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      }
+      wave_sync();
+      mark(kPhLookup);
+      auto res_lp = [&](int u) -> double { return u < kLmRes ? W.lp[u] : scrL[gbase + u]; };
+      // the pair's group: result offset, lookups, mask of the listed homophones
+      const int off = __shfl(roff, lead, 64);
+      const uint32_t gc = static_cast<uint32_t>(__shfl(static_cast<int>(gcnt), lead, 64));
+      const uint64_t gm = static_cast<uint32_t>(__shfl(static_cast<int>(gmask), lead, 64)) |
+                          (static_cast<uint64_t>(static_cast<uint32_t>(__shfl(static_cast<int>(gmask >> 32), lead, 64))) << 32);
+      const uint32_t* const E = scrE + static_cast<size_t>(e0 * kMaxSub + lead) * kMaxExplicit;
+      const bool full = pair && !(gc & kGroupHeavy);
+      const bool walk = pair && (gc & kGroupHeavy);
+      // a word with a group looked up in full over many homophones is ranked by
+      // the whole wavefront below, any other by its four lanes
+      const uint64_t manyb = __ballot(full && Hn > kLaneMaxH);
+      const bool many = ((manyb >> (lane & ~(kMaxSub - 1))) & ((1ull << kMaxSub) - 1ull)) != 0;
+      // this lane's best o: score, j << 16 | h (the order of equal scores), and
+      // the source: its lookup result (>= 0), or, for a homophone that backs off
+      // to its unigram in a heavy group, -1 - its rank in unigram order
+      double tL[kMaxSub];
+      int tq[kMaxSub], ts[kMaxSub];
+#pragma unroll
+      for (int k = 0; k < kMaxSub; ++k) {
+        tL[k] = kNegInf;
+        tq[k] = 0x7FFFFFFF;
+        ts[k] = 0;
+      }
+      auto insert = [&](double L, int qq, int ss) {
+#pragma unroll
+        for (int k = 0; k < kMaxSub; ++k) {
+          if (k < O && (L > tL[k] || (L == tL[k] && qq < tq[k]))) {
+            const double t = tL[k];
+            const int u = tq[k], v = ts[k];
+            tL[k] = L;
+            tq[k] = qq;
+            ts[k] = ss;
+            L = t;
+            qq = u;
+            ss = v;
+          }
+        }
+      };
+      // Katz backoff to the unigram
+      auto unigram_score = [&](const Ctx& c, double lw, float logp) -> double {
+        const double lp = static_cast<double>(c.bo3) +
+                          (static_cast<double>(c.bo2) + (static_cast<double>(c.bo1) + static_cast<double>(logp)));
+        return lw + Pr.comega * lp;
+      };
+      if (!many && pair) {
+        const int nl = static_cast<int>(gc & ~kGroupHeavy);
+        for (int m = 0; m < nl; ++m)
+          insert(Lw + Pr.comega * res_lp(off + m), (j << 16) | static_cast<int>(walk ? E[m] : static_cast<uint32_t>(m)), off + m);
+        if (walk) {
+          // the heavy group's other homophones in unigram order (scores
+          // non-increasing), until its o-th such candidate scores strictly
+          // above the next word's
+          int got = 0;
+          double Lth = HUGE_VAL;
+          for (uint32_t k = 0; k < Hn; ++k) {
+            const WordRank wr = Sr.wrank[woff + k];
+            const double L = unigram_score(ctx, Lw, wr.logp);
+            if (got >= O && Lth > L) break;
+            bool member = false;
+            if ((gm >> (wr.h & 63u)) & 1ull)
+              for (int m = 0; m < nl; ++m) member |= E[m] == wr.h;
+            if (!member) {
+              insert(L, (j << 16) | static_cast<int>(wr.h), -1 - static_cast<int>(k));
+              got += 1;
+              if (got == O) Lth = L;
+            }
+          }
+        }
+      }
+      // o rounds of an arg-max over the word's four lanes; lane k keeps the k-th
+      // winner; lambda is relative to the best
+      double myL = kNegInf, bestL = kNegInf;
+      int myq = 0, mys = 0, kept = 0;
+      bool open = true;
+#pragma unroll
+      for (int k = 0; k < kMaxSub; ++k) {
+        if (k < O) {
+          double bL = tL[0];
+          int bq = tq[0], bs = ts[0];
+          argmax_step<kDppXor1>(&bL, &bq, &bs);
+          argmax_step<kDppXor2>(&bL, &bq, &bs);
+          if (k == 0) bestL = bL;
+          open = open && bL != kNegInf && !(bL < bestL - Pr.lam);
+          if (open) {
+            if (j == k) {
+              myL = bL;
+              myq = bq;
+              mys = bs;
+            }
+            kept = k + 1;
+          }
+          if (tL[0] == bL && tq[0] == bq) {  // the holder (queries are distinct)
+#pragma unroll
+            for (int m = 0; m + 1 < kMaxSub; ++m) {
+              tL[m] = tL[m + 1];
+              tq[m] = tq[m + 1];
+              ts[m] = ts[m + 1];
+            }
+            tL[kMaxSub - 1] = kNegInf;
+            tq[kMaxSub - 1] = 0x7FFFFFFF;
+          }
+        }
+      }
+      // words ranked by the whole wavefront: lane h reads homophone h
+#pragma unroll 1
+      for (uint64_t left = manyb; left;) {
+        const int l0 = __builtin_ctzll(left) & ~(kMaxSub - 1);  // the word's first lane
+        left &= ~(((1ull << kMaxSub) - 1ull) << l0);
+        const int xn = __builtin_amdgcn_readlane(nsub, l0);
+        const int xH = __builtin_amdgcn_readlane(static_cast<int>(Hn), l0);
+        const uint32_t xw = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(woff), l0));
+        double sL[kMaxSub];
+        int sq[kMaxSub], ss[kMaxSub];
+#pragma unroll
+        for (int k = 0; k < kMaxSub; ++k) {
+          sL[k] = kNegInf;
+          sq[k] = 0x7FFFFFFF;
+          ss[k] = 0;
+        }
+        auto put = [&](double L, int qq, int sr) {
+#pragma unroll
+          for (int k = 0; k < kMaxSub; ++k) {
+            if (k < O && (L > sL[k] || (L == sL[k] && qq < sq[k]))) {
+              const double t = sL[k];
+              const int u = sq[k], v = ss[k];
+              sL[k] = L;
+              sq[k] = qq;
+              ss[k] = sr;
+              L = t;
+              qq = u;
+              sr = v;
+            }
+          }
+        };
+#pragma unroll 1
+        for (int jj = 0; jj < xn; ++jj) {
+          const double lw = readlane_f64(Lw, l0 + jj);
+          const uint32_t xc = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(gc), l0 + jj));
+          const int xo = __builtin_amdgcn_readlane(off, l0 + jj);
+          if (!(xc & kGroupHeavy)) {
+            for (int h = lane; h < xH; h += 64) put(lw + Pr.comega * res_lp(xo + h), (jj << 16) | h, xo + h);
+          } else {
+            // lane m holds the m-th listed homophone, a candidate with its
+            // looked-up score; the others in unigram order, 64 at a time, until
+            // the sub-beam has o candidates strictly above all that remain
+            const int xl = __builtin_amdgcn_readlane(lead, l0 + jj);
+            const int ne = static_cast<int>(xc & ~kGroupHeavy);
+            uint32_t eh = kNone;
+            if (lane < ne) {
+              eh = scrE[static_cast<size_t>(e0 * kMaxSub + xl) * kMaxExplicit + lane];
+              put(lw + Pr.comega * res_lp(xo + lane), (jj << 16) | static_cast<int>(eh), xo + lane);
+            }
+            Ctx cx{};
+            cx.bo1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ctx.bo1), l0 + jj));
+            cx.bo2 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ctx.bo2), l0 + jj));
+            cx.bo3 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ctx.bo3), l0 + jj));
+            int cum = 0;
+#pragma unroll 1
+            for (int c0 = 0; c0 < xH; c0 += 64) {
+              const int k = c0 + lane;
+              const bool valid = k < xH;
+              WordRank wr = WordRank{0, 0.0f, 0.0f, kNone};
+              if (valid) wr = Sr.wrank[xw + k];
+              const int last = (xH - 1 - c0) < 63 ? xH - 1 - c0 : 63;
+              bool member = false;
+              for (int m = 0; m < ne; ++m)
+                member |= static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(eh), m)) == wr.h;
+              const double L = unigram_score(cx, lw, wr.logp);
+              const bool cand = valid && !member;
+              if (cand) put(L, (jj << 16) | static_cast<int>(wr.h), -1 - k);
+              const double lastL = readlane_f64(L, last);
+              cum += __popcll(__ballot(cand && L > lastL));
+              if (cum >= O) break;
+            }
+          }
+        }
+        // o rounds of wavefront arg-max; lane l0 + k keeps the k-th winner
+        double xbest = kNegInf;
+        int xkept = 0;
+#pragma unroll 1
+        for (int k = 0; k < O; ++k) {
+          double bL = sL[0];
+          int bq = sq[0];
+          wave_argmax(&bL, &bq);
+          if (bL == kNegInf) break;
+          if (k == 0) xbest = bL;
+          if (bL < xbest - Pr.lam) break;
+          const bool holder = sL[0] == bL && sq[0] == bq;  // one lane: queries are distinct
+          const int hl = __builtin_ctzll(__ballot(holder));
+          const int bs = __builtin_amdgcn_readlane(ss[0], hl);
+          if (lane == l0 + k) {
+            myL = bL;
+            myq = bq;
+            mys = bs;
+          }
+          if (holder) {
+#pragma unroll
+            for (int m = 0; m + 1 < kMaxSub; ++m) {
+              sL[m] = sL[m + 1];
+              sq[m] = sq[m + 1];
+              ss[m] = ss[m + 1];
+            }
+            sL[kMaxSub - 1] = kNegInf;
+            sq[kMaxSub - 1] = 0x7FFFFFFF;
+          }
+          xkept = k + 1;
+        }
+        if ((lane & ~(kMaxSub - 1)) == l0) kept = xkept;
+      }
+      // history nodes (o reserved per word, in order), one lane per kept sub-beam
+      const bool room = static_cast<uint64_t>(arena_n) + static_cast<uint64_t>(e + 1) * O <= Sr.arena_cap;
+      const uint32_t pn =
+          static_cast<uint32_t>(__shfl(static_cast<int>(ph), (lane & ~(kMaxSub - 1)) + ((myq >> 16) & (kMaxSub - 1)), 64));
+      if (word && room && j < kept) {
+        QState st;
+        if (mys >= 0) {
+          st = mys < kLmRes ? W.st[mys] : scrS[gbase + mys];
+        } else {
+          const WordRank wr = Sr.wrank[woff + static_cast<uint32_t>(-1 - mys)];
+          st.c2 = kNone;
+          st.c3 = kNone;
+          st.bo2 = 0.0f;
+          st.bo3 = 0.0f;
+          st.w = wr.w;
+          st.bo1 = wr.bo;
+        }
+        const HistNode par = Sr.arena[pn];
+        HistNode hn;
+        hn.word = st.w;
+        hn.c2 = st.c2;
+        hn.c3 = st.c3;
+        hn.bo1 = st.bo1;
+        hn.bo2 = st.bo2;
+        hn.bo3 = st.bo3;
+        hn.depth = par.depth + 1;
+        hn.sfus = synth ? par.sfus + bigram_score(Pr, par.word, st.w) : 0.0;
+        // a parent that ends a block (the root included) starts a new one
+        const bool starts = par.depth % kHistBlock == 0;
+        hn.blk = starts ? pn : par.blk;
+        hn.w[0] = starts ? -1 : par.word;
+#pragma unroll
+        for (int i = 1; i < kHistBlock - 1; ++i) hn.w[i] = starts ? -1 : par.w[i - 1];
+        const uint32_t node = arena0 + arena_n + static_cast<uint32_t>(e * O + j);
+        Sr.arena[node] = hn;
+        H.Lw[rr * kMaxSub + j] = myL;
+        H.hist[rr * kMaxSub + j] = node;
+      }
+      if (word && j == 0) {
+        if (room)
+          H.meta[rr] = (H.meta[rr] & 0xFFu) | (static_cast<uint32_t>(kept) << 8);
+        else
+          atomicOr(Sr.flags, kFlagArena);
+        c_words += 1;
+        c_queries += static_cast<uint64_t>(nsub) * Hn;
+      }
+      wave_sync();
+      mark(kPhRank);
+    }
+  };
+
+  // the first frame's hypotheses
+  if (wave < RW) recombine(P, sBeam[0], sD[0], n, tid);
+  lds_barrier();
+  mark(kPhRecomb);
 
   for (int tau = tau0; tau < tend; ++tau) {
     // the thread index is made opaque to the optimizer in every frame so that
@@ -786,80 +1335,31 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     asm volatile("" : "+s"(A));
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    BeamLds<KMAX>& C = sBeam[DB ? cur : 0];        // the frame's hypotheses
+    BeamLds<KMAX>& C = sBeam[DB ? cur : 0];        // the frame's hypotheses (recombined)
     BeamLds<KMAX>& N = sBeam[DB ? (cur ^ 1) : 0];  // the new ones (the same buffer when !DB)
+    const double* const Dc = sD[row];              // the frame's scaled log-probs
+    const bool more = tau + 1 < tend;
 
     // the next frame's log-probs are loaded meanwhile
-    if (tid < kClasses && tau + 1 < tend) dnext = logits[(static_cast<size_t>(b) * Tc + tau + 1) * kClasses + tid];
-    unsigned long long* const hkey = sHKey;  // the frame's prefix keys (inserted with the hypotheses)
+    if (wave == NW - 1 && lane < kClasses && more)
+      dnext = logits[(static_cast<size_t>(b) * Tc + tau + 1) * kClasses + lane];
     for (int d = tid; d < kBins; d += BLOCK) sHisto[d] = 0;
     if (tid == 0) sBCount = 0;
-    uint64_t my_pkey = kNoParent;
-    uint32_t my_meta = 0;
-    if (tid < n) {
-      my_pkey = C.pkey[tid];
-      my_meta = C.meta[tid];
-    }
-
-    // ---- recombination: a hypothesis whose parent prefix is also live receives
-    // the parent's extension by its last symbol; that extension is removed from
-    // the parent's fan-out.  Stay candidates: blank-stay, repeat-stay, merged
-    // parent extension.
-    double st = kNegInf, up = kNegInf;  // this hypothesis' stay score and extension bound
-    if (tid < n) {
-      int par = -1;
-      if (my_pkey != kNoParent) {
-        uint32_t s = static_cast<uint32_t>(my_pkey) & (HS - 1);
-        for (int probes = 0; probes < HS; ++probes) {
-          const unsigned long long k = hkey[s];
-          if (k == kEmptyKey) break;
-          if (k == my_pkey) {
-            par = static_cast<int>(sHIdx[s]);
-            break;
-          }
-          s = (s + 1) & (HS - 1);
-        }
-        if (par >= 0) atomicAnd(reinterpret_cast<unsigned long long*>(&sMask[par]), ~(1ull << (my_meta & 0xFF)));
-      }
-      const int last = my_meta & 0xFF;
-      const double ab2 = C.pt[tid] + sD[0];
-      const double rep = last ? C.anb[tid] + sD[last] : kNegInf;
-      double ext = kNegInf;
-      if (par >= 0) {
-        const double base = (last == static_cast<int>(C.meta[par] & 0xFF)) ? C.ab[par] : C.pt[par];
-        ext = (base + sD[last]) + (last == kSep ? P.gamma : P.beta);
-      }
-      // anb2 = merge(rep, ext), then pt2 = merge(ab2, anb2); merge is
-      // log-sum-exp, or max for the best-alignment recombination
-      double x = rep, y = ext, anb2 = 0.0;
-#pragma unroll 1
-      for (int pass = 0; pass < 2; ++pass) {
-        const double l = P.merge_max ? fmax(x, y) : lse2(x, y, [&](int k) { return sAtanh[k]; });
-        if (pass == 0) {
-          anb2 = l;
-          x = ab2;
-          y = l;
-        } else {
-          y = l;
-        }
-      }
-      const double pt2 = y;
-      sAb2[tid] = ab2;
-      sAnb2[tid] = anb2;
-      sPt2[tid] = pt2;
-      st = pt2 + C.Lw[tid * kMaxSub];
-      sStay[tid] = st;
-      // no extension of this hypothesis scores above this (each of the additions
-      // rounds monotonically, base <= pt, log-prob <= sDmax, bonus <= the larger)
-      if constexpr (kOnePass) up = ((C.pt[tid] + sDmax) + fmax(P.beta, P.gamma)) + C.Lw[tid * kMaxSub];
-    }
+    for (int s = tid; s < HS; s += BLOCK) sHKey[s] = kEmptyKey;  // for the new hypotheses' keys
     if constexpr (kOnePass) {
       // per wavefront: an upper bound of every candidate (sRedB[w]), the best
       // stay (sRedB[NW + w]) and the lowest (sRedB[2 NW + w]), for the top-K's
-      // bin range (a wavefront past the last hypothesis, e.g. the upper half
-      // of the block when there is one thread per hypothesis here but two
-      // lanes per hypothesis later, has the neutral values without reducing)
+      // bin range (a wavefront past the last hypothesis has the neutral values
+      // without reducing)
       if (wave * 64 < n) {
+        double st = kNegInf, up = kNegInf;
+        if (tid < n) {
+          const double lw = C.Lw[tid * kMaxSub];
+          st = sPt2[tid] + lw;
+          // no extension of this hypothesis scores above this (each of the additions
+          // rounds monotonically, base <= pt, log-prob <= sDmax, bonus <= the larger)
+          up = ((C.pt[tid] + sDmax[row]) + fmax(P.beta, P.gamma)) + lw;
+        }
         double hi = fmax(st, up), nlo = -st;
         wave_minmax(&hi, &nlo);
         const double nmin = wave_max(tid < n ? -st : -HUGE_VAL);
@@ -876,7 +1376,6 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     }
     lds_barrier();
     mark(kPhRecomb);
-    for (int s = tid; s < HS; s += BLOCK) sHKey[s] = kEmptyKey;  // for the new hypotheses' keys
     // Workgroups that share a CU: the CU's arbitration favours the older
     // wavefronts, so the workgroup dispatched second (the later half of the
     // grid, when workgroups are dispatched to the CUs in order) fell behind
@@ -887,6 +1386,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       __builtin_amdgcn_s_setprio(1);
     else
       __builtin_amdgcn_s_setprio(0);
+
 
     // ---- this lane's candidates: slot k is the extension by v = 1 + ln + LPB*k,
     // plus the merged stay on lane 0; scores are recomputed in every pass (same
@@ -904,10 +1404,10 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       // slot k <-> symbol 1 + ln + LPB*k: bit LPB*k of c_rel is its mask bit
       // (slots past the separator are invalid: the mask is cut to bits 1..40,
       // its bits 48..63 hold the node's word count)
-      c_rel = (sMask[hi_] & ((2ull << kSep) - 1ull)) >> (1 + ln);
+      c_rel = (C.tmask[hi_] & ~sCut[hi_] & ((2ull << kSep) - 1ull)) >> (1 + ln);
       c_rep = static_cast<int>(C.meta[hi_] & 0xFF) - 1 - ln;  // LPB*k of the repeat symbol
       c_key = C.key[hi_];
-      if (ln == 0) c_stay = sStay[hi_];
+      if (ln == 0) c_stay = sPt2[hi_] + c_L;
     }
     // the separator (symbol kSep = 1 + ln + LPB*k) can only be slot
     // (kSep - 1) / LPB of lane (kSep - 1) % LPB: with k known at compile time
@@ -926,12 +1426,12 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     double c_rps = kNegInf;   // its score
     if (c_rep >= 0 && c_rep % LPB == 0 && ((c_rel >> c_rep) & 1ull)) {
       c_rk = c_rep / LPB;
-      c_rps = ((c_ab + sD[1 + ln + c_rep]) + bonus_at(c_rk)) + c_L;
+      c_rps = ((c_ab + Dc[1 + ln + c_rep]) + bonus_at(c_rk)) + c_L;
       c_rel &= ~(1ull << c_rep);
     }
     auto score_now = [&](int k) -> double {
       const bool valid = (c_rel >> (LPB * k)) & 1ull;
-      const double sc = ((c_p + sD[1 + ln + LPB * k]) + bonus_at(k)) + c_L;
+      const double sc = ((c_p + Dc[1 + ln + LPB * k]) + bonus_at(k)) + c_L;
       return valid ? sc : kNegInf;
     };
     auto key_of = [&](int v) -> uint64_t { return v == 0 ? c_key : prefix_step(c_key, v); };
@@ -1082,7 +1582,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         // branch-free: the score and bin of the slot, valid or not (a bin in
         // range either way), then a select
         const bool valid = (c_rel >> (LPB * k)) & 1ull;
-        const double sc = ((c_p + sD[1 + ln + LPB * k]) + bonus_at(k)) + c_L;
+        const double sc = ((c_p + Dc[1 + ln + LPB * k]) + bonus_at(k)) + c_L;
         const bool in = valid && sc >= L0;
         const uint32_t bn = in ? static_cast<uint32_t>(bin_lv0(sc)) : 0xFFFFu;
         if (k & 1)
@@ -1111,6 +1611,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       if (bn != 0xFFFFu) atomicAdd(&sHisto[bn], 1u);
     }
     lds_barrier();
+    if (wave == NW - 1 && more) set_row(P, row ^ 1, dnext);
     // With bounds, the exact best is needed only if the K-th candidate may lie
     // at or below U - theta (>= best - theta): when it lies in a bin above that
     // value's, every candidate up to it is above the cut, which cannot bind.
@@ -1309,17 +1810,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     mark(kPhTopK);
 
     // ---- the new hypotheses; an extension's trie node is fetched now and
-    // stored after the LM step.  (The n-gram grouping table is cleared here:
-    // the top-K scratch it shares is no longer read.)
-    {
-      unsigned long long* const gk = reinterpret_cast<unsigned long long*>(sSel);
-      for (int q = tid; q < NPL; q += BLOCK) gk[q] = kEmptyKey;
-      if (tid == 0) {
-        sNG = 0;
-        sHeavy = 0;
-        sNLarge = 0;
-      }
-    }
+    // stored after the next frame's recombination
     const int r = tid;
     int is_event = 0;
     uint32_t ev_woff = 0, ev_H = 0;
@@ -1348,7 +1839,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       } else {
         const int last = meta_i & 0xFF;
         const double base = (v == last) ? C.ab[i] : C.pt[i];
-        const double anb = (base + sD[v]) + (v == kSep ? P.gamma : P.beta);
+        const double anb = (base + Dc[v]) + (v == kSep ? P.gamma : P.beta);
         const uint64_t tm = C.tmask[i];
         w_key = prefix_step(C.key[i], v);
         w_pkey = C.key[i];
@@ -1386,6 +1877,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     if constexpr (!DB) lds_barrier();  // every source entry has been read
     if (r < nsel) {
       insert_key(w_key, r);  // for the next frame's parent lookups
+      sCut[r] = 0;
       N.key[r] = w_key;
       N.pkey[r] = w_pkey;
       N.ab[r] = w_ab;
@@ -1395,7 +1887,6 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       N.meta[r] = w_meta;
       if (!tn_load) {
         N.tmask[r] = w_tmask;
-        sMask[r] = w_tmask;
         N.first[r] = w_first;
         N.woff[r] = w_woff;
       }
@@ -1407,530 +1898,37 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         }
       }
     }
-    int nev = 0;
-    const int erank = block_scan<BLOCK, false>(is_event, sScanC, &nev);
-    if (is_event) {
-      sEvBeam[erank] = static_cast<uint32_t>(r);
-      sEvWoff[erank] = ev_woff;
-      sEvH[erank] = ev_H;
+    if (wave < RW) {
+      const uint64_t evs = __ballot(is_event);
+      if (is_event) {
+        const int k = 64 * wave + __popcll(evs & ((1ull << lane) - 1ull));
+        sEvBeam[k] = static_cast<uint32_t>(r);
+        sEvWoff[k] = ev_woff;
+        sEvH[k] = ev_H;
+      }
+      if (lane == 0) sEvCnt[wave] = __popcll(evs);
     }
+    lds_barrier();  // the new hypotheses, their keys and the completed words are in place
     mark(kPhNewBeam);
+    int nev = 0;
+#pragma unroll
+    for (int w = 0; w < RW; ++w) nev += sEvCnt[w];
 
-    // ---- Eq. (1).  The queries (sub-beam j, homophone h) of the completed
-    // words are scored once per distinct group (n-gram context, completed-word
-    // node): the pairs (word e, sub-beam j) are grouped in an LDS hash table,
-    // the groups' lookups spread over all threads into the stream's scratch,
-    // and each completed word ranks its queries from there.  Words are taken
-    // in batches of NEB (the grouping tables hold NPL pairs).
-    unsigned long long* const sGKey = reinterpret_cast<unsigned long long*>(sSel);
-    int32_t* const sGId = reinterpret_cast<int32_t*>(sSel + 8 * NPL);
-    int32_t* const sPairG = sGId + NPL;  // pair -> hash slot, then -> group
-    uint32_t* const sGwoff = reinterpret_cast<uint32_t*>(sPairG + NPL);
-    uint32_t* const sGH = sGwoff + NPL;
-    Ctx* const sGctx = reinterpret_cast<Ctx*>(sGH + NPL);             // 24 B each
-    int32_t* const sGoff = reinterpret_cast<int32_t*>(sGctx + NPL);  // NPL + 1 entries
-    uint32_t* const sGcnt = reinterpret_cast<uint32_t*>(sGoff + NPL + 1);  // lookups | kGroupHeavy
-    // heavy groups: bit (h mod 64) set for each homophone h of the explicit
-    // list; past sGcnt (which ends 56 NPL + 4 bytes in), 8-B aligned
-    constexpr int kGmaskOff = (56 * NPL + 4 + 7) & ~7;
-    uint64_t* const sGmask = reinterpret_cast<uint64_t*>(sSel + kGmaskOff);
-    static_assert(kGmaskOff + 8 * NPL <= UNI_BYTES, "grouping tables fit the shared scratch");
-    static_assert(sizeof(Ctx) == 24, "group contexts are 24 B each");
-#pragma unroll 1
-    for (int e0 = 0; e0 < nev; e0 += NEB) {
-    const int nb = nev - e0 < NEB ? nev - e0 : NEB;
-    if (e0 > 0) {
-      // the next batch: the previous one's scratch reads are done; fresh grouping table
-      __syncthreads();
-      for (int q = tid; q < NPL; q += BLOCK) sGKey[q] = kEmptyKey;
-      if (tid == 0) {
-        sNG = 0;
-        sHeavy = 0;
-        sNLarge = 0;
-      }
+    // ---- Eq. (1) for the completed words, and, on the wavefronts that hold the
+    // hypotheses, the next frame's recombination, which needs none of its
+    // results: neither waits for the other.  (An instance with no wavefront
+    // to spare scores first.)
+    if (!kSplit || (wave >= RW && wave < RW + LMW)) {
+      score_words(P, S, N, nev, kSplit ? wave - RW : wave, LMW, lane);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // history nodes: read by the fusion and the next frames
     }
-    lds_barrier();
-    for (int pr = tid; pr < nb * kMaxSub; pr += BLOCK) {
-      const int el = pr / kMaxSub;
-      const int e = e0 + el;
-      const int j = pr - el * kMaxSub;
-      const uint32_t rr = sEvBeam[e];
-      int slot = -1;
-      if (j < static_cast<int>((N.meta[rr] >> 8) & 0xFF)) {
-        const uint32_t ph = N.hist[rr * kMaxSub + j];
-        const Ctx ctx = ctx_of(S.arena[ph]);
-        const unsigned long long key = group_key(ctx, sEvWoff[e]);
-        uint32_t q = static_cast<uint32_t>(splitmix64(key)) & (NPL - 1);
-        for (;;) {
-          const unsigned long long prev = atomicCAS(&sGKey[q], kEmptyKey, key);
-          if (prev == kEmptyKey) {
-            const int g = atomicAdd(&sNG, 1);
-            sGId[q] = g;
-            sGwoff[g] = sEvWoff[e];
-            sGH[g] = sEvH[e];
-            sGctx[g] = ctx;
-            if (sEvH[e] >= P.heavy_min) sHeavy = 1;
-            break;
-          }
-          if (prev == key) break;
-          q = (q + 1) & (NPL - 1);
-        }
-        slot = static_cast<int>(q);
+    if (wave < RW) {
+      if (more) recombine(P, N, sD[row ^ 1], nsel, tid);
+      if (tn_load) {
+        N.tmask[r] = tn.mask;
+        N.first[r] = tn.first_child;
+        N.woff[r] = tn.word_off;
       }
-      sPairG[pr] = slot;
-    }
-    lds_barrier();
-    const int NG = sNG;
-    for (int pr = tid; pr < nb * kMaxSub; pr += BLOCK) {
-      const int q = sPairG[pr];
-      if (q >= 0) sPairG[pr] = sGId[q];
-    }
-    // heavy groups (nodes with many homophones): the homophones with an explicit
-    // n-gram for the group's context, from the continuation index (each once: a
-    // homophone can be listed for several context orders); the others back off
-    // to their unigrams and are not looked up.  A group with more than
-    // kMaxExplicit listed is looked up in full.
-    const bool heavy_frame = sHeavy != 0;
-    for (int g = tid; g < NG; g += BLOCK) {
-      const uint32_t Hg = sGH[g];
-      uint32_t cnt = Hg;
-      if (Hg >= P.heavy_min) {
-        PresHit hit[3];
-        pres_lookup(S, sGctx[g], sGwoff[g], hit, &plines);
-        const uint32_t ne = hit[0].n + hit[1].n + hit[2].n;
-        if (ne <= static_cast<uint32_t>(kMaxExplicit)) {
-          uint32_t* const E = scrE + static_cast<size_t>(g) * kMaxExplicit;
-          uint64_t bm = 0;
-          uint32_t nd = 0;
-          // (the list is read back only when the mask bit is already set)
-          auto add = [&](uint32_t x) {
-            const uint64_t bit = 1ull << (x & 63u);
-            bool seen = false;
-            if (bm & bit)
-              for (uint32_t m = 0; m < nd; ++m) seen |= E[m] == x;
-            if (!seen) {
-              E[nd++] = x;
-              bm |= bit;
-            }
-          };
-#pragma unroll
-          for (int o3 = 0; o3 < 3; ++o3) {
-            if (hit[o3].n == 1) {
-              add(hit[o3].a);
-            } else {
-              const uint32_t* lst = (o3 == 0 ? S.p2.lists : (o3 == 1 ? S.p3.lists : S.p4.lists)) + hit[o3].a;
-              for (uint32_t m = 0; m < hit[o3].n; ++m) add(lst[m]);
-            }
-          }
-          cnt = nd | kGroupHeavy;
-          sGmask[g] = bm;
-        }
-      }
-      sGcnt[g] = cnt;
-    }
-    if (heavy_frame)
-      __syncthreads();  // the explicit lists (global memory) are read by other threads
-    else
-      lds_barrier();
-    // lookup offsets of the groups
-    int U = 0;
-    {
-      constexpr int PG = (NPL + BLOCK - 1) / BLOCK;
-      int loc = 0;
-#pragma unroll
-      for (int q = 0; q < PG; ++q) {
-        const int g = tid * PG + q;
-        loc += g < NG ? static_cast<int>(sGcnt[g] & ~kGroupHeavy) : 0;
-      }
-      int pre = block_scan<BLOCK, false>(loc, sScanD, &U);
-#pragma unroll
-      for (int q = 0; q < PG; ++q) {
-        const int g = tid * PG + q;
-        if (g < NG) {
-          sGoff[g] = pre;
-          pre += static_cast<int>(sGcnt[g] & ~kGroupHeavy);
-        }
-      }
-      if (tid == 0) sGoff[NG] = U;
-    }
-    if (static_cast<uint64_t>(U) > S.scap) {  // cannot happen: U <= K * O * (largest homophone set)
-      if (tid == 0) atomicOr(S.flags, kFlagSelect);
-      U = 0;
-    }
-    if (tid == 0) sCnt[6] += static_cast<unsigned long long>(U);
-    // the results go to LDS when they fit in the grouping keys freed above (the
-    // usual case), else to the stream's scratch in global memory; the log-probs,
-    // read for every candidate (the states only for the kept ones), stay in
-    // LDS up to four times as many lookups, the states then in the scratch
-    constexpr int kLdsRes = 12 * NPL / 32;
-    constexpr int kLdsLp = 12 * NPL / 8;
-    double* const sResL = reinterpret_cast<double*>(sSel);
-    QState* const sResS = reinterpret_cast<QState*>(sSel + 8 * kLdsRes);  // (only when U <= kLdsRes)
-    const bool res_lds = U <= kLdsRes;
-    const bool lp_lds = U <= kLdsLp;
-    auto res_lp = [&](int u) -> double { return lp_lds ? sResL[u] : scrL[u]; };
-    auto res_st = [&](int u) -> QState { return res_lds ? sResS[u] : scrS[u]; };
-    lds_barrier();
-    mark(kPhGroup);
-    for (int u = tid; u < U; u += BLOCK) {
-      int lo = 0, hi = NG - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (sGoff[mid] <= u) lo = mid; else hi = mid - 1;
-      }
-      const uint32_t k = static_cast<uint32_t>(u - sGoff[lo]);
-      const uint32_t h = (sGcnt[lo] & kGroupHeavy) ? scrE[static_cast<size_t>(lo) * kMaxExplicit + k] : k;
-      const int32_t w = S.trie_words[sGwoff[lo] + h];
-      const LmResult res = lm_lookup(S, w, sGctx[lo], &lines);
-      if (lp_lds)
-        sResL[u] = res.lp;
-      else
-        scrL[u] = res.lp;
-      if (res_lds)
-        sResS[u] = res.st;
-      else
-        scrS[u] = res.st;
-    }
-    if (res_lds)
-      lds_barrier();
-    else
-      __syncthreads();  // the lookup results (global memory) are read by other threads
-    mark(kPhLookup);
-    // each completed word: its top-o by (score desc, j*H + h asc), lambda
-    // pruning, word-history nodes (o reserved per word, in order).  A
-    // candidate's source: its lookup result in the scratch (>= 0), or, for a
-    // homophone that backs off to its unigram in a heavy group, -1 - its rank
-    // in the node's unigram order.  A word is ranked by one thread, unless one
-    // of its sub-beams' groups was looked up in full over more than
-    // kThreadMaxH homophones: those words get a wavefront each.
-    // (ph: the winner's parent history, read before any of the word's
-    // sub-beams is overwritten)
-    auto write_node = [&](int e, int k, double L, uint32_t ph, int src) {
-      const uint32_t rr = sEvBeam[e];
-      QState st;
-      if (src >= 0) {
-        st = res_st(src);
-      } else {
-        const WordRank wr = S.wrank[sEvWoff[e] + static_cast<uint32_t>(-1 - src)];
-        st.c2 = kNone;
-        st.c3 = kNone;
-        st.bo2 = 0.0f;
-        st.bo3 = 0.0f;
-        st.w = wr.w;
-        st.bo1 = wr.bo;
-      }
-      const HistNode par = S.arena[ph];
-      HistNode hn;
-      hn.word = st.w;
-      hn.c2 = st.c2;
-      hn.c3 = st.c3;
-      hn.bo1 = st.bo1;
-      hn.bo2 = st.bo2;
-      hn.bo3 = st.bo3;
-      hn.depth = par.depth + 1;
-      hn.sfus = synth ? par.sfus + bigram_score(P, par.word, st.w) : 0.0;
-      // a parent that ends a block (the root included) starts a new one
-      const bool starts = par.depth % kHistBlock == 0;
-      hn.blk = starts ? ph : par.blk;
-      hn.w[0] = starts ? -1 : par.word;
-#pragma unroll
-      for (int i = 1; i < kHistBlock - 1; ++i) hn.w[i] = starts ? -1 : par.w[i - 1];
-      const uint32_t node = arena0 + arena_n + static_cast<uint32_t>(e * O + k);
-      S.arena[node] = hn;
-      N.Lw[rr * kMaxSub + k] = L;
-      N.hist[rr * kMaxSub + k] = node;
-    };
-    auto close_event = [&](int e, int kept, int nsub) {
-      const uint32_t rr = sEvBeam[e];
-      const bool room = static_cast<uint64_t>(arena_n) + static_cast<uint64_t>(e + 1) * O <= S.arena_cap;
-      if (room)
-        N.meta[rr] = (N.meta[rr] & 0xFFu) | (static_cast<uint32_t>(kept) << 8);
-      else
-        atomicOr(S.flags, kFlagArena);
-      c_words += 1;
-      c_queries += static_cast<uint64_t>(nsub * sEvH[e]);
-    };
-    {
-      constexpr uint32_t kThreadMaxH = 16;
-      bool mine = false;
-      if (tid < nb) {
-        const int nsub = (N.meta[sEvBeam[e0 + tid]] >> 8) & 0xFF;
-        bool large = false;
-        for (int j = 0; j < nsub; ++j) {
-          const int g = sPairG[tid * kMaxSub + j];
-          large |= !(sGcnt[g] & kGroupHeavy) && sGH[g] > kThreadMaxH;
-        }
-        if (large)
-          sLarge[atomicAdd(&sNLarge, 1)] = e0 + tid;
-        else
-          mine = true;
-      }
-      if (mine) {
-        const int e = e0 + tid;
-        const uint32_t rr = sEvBeam[e];
-        const int H = static_cast<int>(sEvH[e]);
-        const uint32_t woff = sEvWoff[e];
-        const int nsub = (N.meta[rr] >> 8) & 0xFF;
-        double tL[kMaxSub];
-        int tq[kMaxSub], ts[kMaxSub];
-#pragma unroll
-        for (int k = 0; k < kMaxSub; ++k) {
-          tL[k] = kNegInf;
-          tq[k] = 0x7FFFFFFF;
-          ts[k] = 0;
-        }
-        auto insert = [&](double L, int qq, int ss) {
-#pragma unroll
-          for (int k = 0; k < kMaxSub; ++k) {
-            if (k < O && (L > tL[k] || (L == tL[k] && qq < tq[k]))) {
-              const double t = tL[k];
-              const int u = tq[k], v = ts[k];
-              tL[k] = L;
-              tq[k] = qq;
-              ts[k] = ss;
-              L = t;
-              qq = u;
-              ss = v;
-            }
-          }
-        };
-        bool any_heavy = false;
-#pragma unroll
-        for (int j = 0; j < kMaxSub; ++j) {
-          if (j < nsub) {
-            const double Lw = N.Lw[rr * kMaxSub + j];
-            const int g = sPairG[(e - e0) * kMaxSub + j];
-            const int off = sGoff[g];
-            const uint32_t cnt = sGcnt[g];
-            if (!(cnt & kGroupHeavy)) {
-              for (int h = 0; h < H; ++h) insert(Lw + P.comega * res_lp(off + h), j * H + h, off + h);
-            } else {
-              any_heavy = true;
-              const uint32_t* E = scrE + static_cast<size_t>(g) * kMaxExplicit;
-              const int ne = static_cast<int>(cnt & ~kGroupHeavy);
-              for (int m = 0; m < ne; ++m)
-                insert(Lw + P.comega * res_lp(off + m), j * H + static_cast<int>(E[m]), off + m);
-            }
-          }
-        }
-        if (any_heavy) {
-          // the heavy groups' other homophones in unigram order (scores
-          // non-increasing): a sub-beam is done once its o-th such candidate
-          // scores strictly above the next word's
-          int nw[kMaxSub];
-          double Lth[kMaxSub];
-#pragma unroll
-          for (int j = 0; j < kMaxSub; ++j) {
-            nw[j] = 0;
-            Lth[j] = HUGE_VAL;
-          }
-#pragma unroll 1
-          for (int k = 0; k < H; ++k) {
-            const WordRank wr = S.wrank[woff + k];
-            bool need = false;
-#pragma unroll
-            for (int j = 0; j < kMaxSub; ++j) {
-              if (j < nsub) {
-                const int g = sPairG[(e - e0) * kMaxSub + j];
-                const uint32_t cnt = sGcnt[g];
-                if (cnt & kGroupHeavy) {
-                  const Ctx cx = sGctx[g];
-                  const double lp = static_cast<double>(cx.bo3) +
-                                    (static_cast<double>(cx.bo2) +
-                                     (static_cast<double>(cx.bo1) + static_cast<double>(wr.logp)));
-                  const double L = N.Lw[rr * kMaxSub + j] + P.comega * lp;
-                  if (nw[j] < O || !(Lth[j] > L)) {
-                    need = true;
-                    bool member = false;
-                    if ((sGmask[g] >> (wr.h & 63u)) & 1ull) {
-                      const uint32_t* E = scrE + static_cast<size_t>(g) * kMaxExplicit;
-                      const int ne = static_cast<int>(cnt & ~kGroupHeavy);
-                      for (int m = 0; m < ne; ++m) member |= E[m] == wr.h;
-                    }
-                    if (!member) {
-                      insert(L, j * H + static_cast<int>(wr.h), -1 - k);
-                      nw[j] += 1;
-                      if (nw[j] == O) Lth[j] = L;
-                    }
-                  }
-                }
-              }
-            }
-            if (!need) break;
-          }
-        }
-        int kept = 0;
-#pragma unroll
-        for (int k = 0; k < kMaxSub; ++k)
-          if (k < O && tL[k] != kNegInf && !(tL[k] < tL[0] - P.lam)) kept = k + 1;
-        const bool room = static_cast<uint64_t>(arena_n) + static_cast<uint64_t>(e + 1) * O <= S.arena_cap;
-        uint32_t ph[kMaxSub];
-#pragma unroll
-        for (int k = 0; k < kMaxSub; ++k) ph[k] = k < kept ? N.hist[rr * kMaxSub + tq[k] / H] : 0u;
-#pragma unroll
-        for (int k = 0; k < kMaxSub; ++k)
-          if (k < kept && room) write_node(e, k, tL[k], ph[k], ts[k]);
-        close_event(e, kept, nsub);
-      }
-    }
-    lds_barrier();  // the list of wavefront-ranked words
-    const int nlarge = sNLarge;
-    for (int x = wave; x < nlarge; x += NW) {
-      const int e = sLarge[x];
-      const uint32_t rr = sEvBeam[e];
-      const uint32_t H = sEvH[e];
-      const uint32_t woff = sEvWoff[e];
-      const int nsub = (N.meta[rr] >> 8) & 0xFF;
-      double tL[kMaxSub];
-      int tq[kMaxSub], ts[kMaxSub];
-#pragma unroll
-      for (int k = 0; k < kMaxSub; ++k) {
-        tL[k] = kNegInf;
-        tq[k] = 0x7FFFFFFF;
-        ts[k] = 0;
-      }
-      auto insert = [&](double L, int qq, int ss) {
-#pragma unroll
-        for (int k = 0; k < kMaxSub; ++k) {
-          if (k < O && (L > tL[k] || (L == tL[k] && qq < tq[k]))) {
-            const double t = tL[k];
-            const int u = tq[k], v = ts[k];
-            tL[k] = L;
-            tq[k] = qq;
-            ts[k] = ss;
-            L = t;
-            qq = u;
-            ss = v;
-          }
-        }
-      };
-      // the sub-beams' scores, groups and result offsets (a group's results
-      // are contiguous in the scratch)
-      double Lw[kMaxSub];
-      int gid[kMaxSub], goff[kMaxSub];
-      uint32_t gcnt[kMaxSub];
-      bool any_full = false, any_heavy = false;
-#pragma unroll
-      for (int j = 0; j < kMaxSub; ++j) {
-        const int jj = j < nsub ? j : 0;
-        Lw[j] = N.Lw[rr * kMaxSub + jj];
-        gid[j] = sPairG[(e - e0) * kMaxSub + jj];
-        goff[j] = sGoff[gid[j]];
-        gcnt[j] = sGcnt[gid[j]];
-        if (j < nsub) {
-          any_heavy |= (gcnt[j] & kGroupHeavy) != 0;
-          any_full |= (gcnt[j] & kGroupHeavy) == 0;
-        }
-      }
-      // full groups: lane h reads homophone h of every such sub-beam
-      if (any_full) {
-        for (int h = lane; h < static_cast<int>(H); h += 64) {
-          double a[kMaxSub];
-#pragma unroll
-          for (int j = 0; j < kMaxSub; ++j)
-            a[j] = (j < nsub && !(gcnt[j] & kGroupHeavy)) ? res_lp(goff[j] + h) : 0.0;
-#pragma unroll
-          for (int j = 0; j < kMaxSub; ++j)
-            if (j < nsub && !(gcnt[j] & kGroupHeavy))
-              insert(Lw[j] + P.comega * a[j], j * static_cast<int>(H) + h, goff[j] + h);
-        }
-      }
-      if (any_heavy) {
-        // heavy groups: lane m holds the m-th explicit homophone (the list has
-        // no repeats), a candidate with its looked-up score
-        uint32_t eh[kMaxSub];
-        int ne[kMaxSub];
-#pragma unroll
-        for (int j = 0; j < kMaxSub; ++j) {
-          const bool hv = j < nsub && (gcnt[j] & kGroupHeavy);
-          ne[j] = hv ? static_cast<int>(gcnt[j] & ~kGroupHeavy) : 0;
-          eh[j] = lane < ne[j] ? scrE[static_cast<size_t>(gid[j]) * kMaxExplicit + lane] : kNone;
-        }
-#pragma unroll
-        for (int j = 0; j < kMaxSub; ++j) {
-          if (ne[j] > 0) {
-            if (lane < ne[j])
-              insert(Lw[j] + P.comega * res_lp(goff[j] + lane), j * static_cast<int>(H) + static_cast<int>(eh[j]),
-                     goff[j] + lane);
-          }
-        }
-        // the other homophones of a heavy group score bo3 + bo2 + bo1 + log10 p1(w)
-        // (Katz backoff to the unigram), monotone in log10 p1: walk the node's
-        // words in unigram order, 64 at a time, until every heavy sub-beam has
-        // o candidates strictly above all that remain
-        int cum[kMaxSub];
-        Ctx cx[kMaxSub];
-#pragma unroll
-        for (int j = 0; j < kMaxSub; ++j) {
-          cum[j] = 0;
-          cx[j] = sGctx[gid[j]];
-        }
-#pragma unroll 1
-        for (int c0 = 0; c0 < static_cast<int>(H); c0 += 64) {
-          const int k = c0 + lane;
-          const bool valid = k < static_cast<int>(H);
-          WordRank wr = WordRank{0, 0.0f, 0.0f, kNone};
-          if (valid) wr = S.wrank[woff + k];
-          const int last = (static_cast<int>(H) - 1 - c0) < 63 ? static_cast<int>(H) - 1 - c0 : 63;
-          bool more = false;
-#pragma unroll
-          for (int j = 0; j < kMaxSub; ++j) {
-            if (j < nsub && (gcnt[j] & kGroupHeavy)) {
-              bool member = false;
-              for (int m = 0; m < ne[j]; ++m)
-                member |= static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(eh[j]), m)) == wr.h;
-              const double lp = static_cast<double>(cx[j].bo3) +
-                                (static_cast<double>(cx[j].bo2) +
-                                 (static_cast<double>(cx[j].bo1) + static_cast<double>(wr.logp)));
-              const double L = Lw[j] + P.comega * lp;
-              const bool cand = valid && !member;
-              if (cand) insert(L, j * static_cast<int>(H) + static_cast<int>(wr.h), -1 - k);
-              const double lastL = readlane_f64(L, last);
-              cum[j] += __popcll(__ballot(cand && L > lastL));
-              more |= cum[j] < O;
-            }
-          }
-          if (!more) break;
-        }
-      }
-      // O rounds of wavefront arg-max; lane k keeps the k-th winner
-      double myL = kNegInf, bestL = kNegInf;
-      int myq = 0, mys = 0, kept = 0;
-#pragma unroll 1
-      for (int k = 0; k < O; ++k) {
-        double bL = tL[0];
-        int bq = tq[0];
-        wave_argmax(&bL, &bq);
-        if (bL == kNegInf) break;
-        if (k == 0) bestL = bL;
-        if (bL < bestL - P.lam) break;
-        const bool holder = tL[0] == bL && tq[0] == bq;  // one lane: queries are distinct
-        const int hl = __builtin_ctzll(__ballot(holder));
-        const int bs = __builtin_amdgcn_readlane(ts[0], hl);
-        if (lane == k) {
-          myL = bL;
-          myq = bq;
-          mys = bs;
-        }
-        if (holder) {
-#pragma unroll
-          for (int m = 0; m + 1 < kMaxSub; ++m) {
-            tL[m] = tL[m + 1];
-            tq[m] = tq[m + 1];
-            ts[m] = ts[m + 1];
-          }
-          tL[kMaxSub - 1] = kNegInf;
-          tq[kMaxSub - 1] = 0x7FFFFFFF;
-        }
-        kept = k + 1;
-      }
-      const bool room = static_cast<uint64_t>(arena_n) + static_cast<uint64_t>(e + 1) * O <= S.arena_cap;
-      // every lane reads its parent before any lane writes (one wavefront, in order)
-      const uint32_t ph = lane < kept ? N.hist[rr * kMaxSub + static_cast<uint32_t>(myq) / H] : 0u;
-      if (lane < kept && room) write_node(e, lane, myL, ph, mys);
-      if (lane == 0) close_event(e, kept, nsub);
-    }
-    mark(kPhRank);
     }
     {
       // nodes reserved this frame; past the capacity the count stays at cap + 1
@@ -1940,15 +1938,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     }
     if (tid == 0) sCnt[4] += static_cast<unsigned long long>(n) * kClasses;
     n = nsel;
-    __syncthreads();  // history nodes (global memory) are read by the fusion and the next frame
-    mark(kPhRank);
-    if (tn_load) {
-      N.tmask[r] = tn.mask;
-      sMask[r] = tn.mask;
-      N.first[r] = tn.first_child;
-      N.woff[r] = tn.word_off;
-    }
-    if (wave == 0 && tau + 1 < tend) set_row(P, dnext);  // this frame's row is no longer read
+    row ^= 1;
+    lds_barrier();
+    mark(kPhRecomb);
 
     // ---- Eq. (2) on fusion frames: the top-F hypotheses by (total desc, key
     // asc); each sub-beam's score becomes phi * its synthetic fusion score and
@@ -2118,9 +2110,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         }
       }
       if (tid == 0) sCnt[5] += static_cast<unsigned long long>(F);
+      lds_barrier();
+      mark(kPhFusion);
     }
-    lds_barrier();
-    mark(kPhFusion);
     if constexpr (DB) cur ^= 1;
   }
 
@@ -2152,6 +2144,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     c_queries += __shfl_xor(c_queries, o, 64);
   }
   if (lane == 0) {
+    atomicAdd(&sCnt[6], static_cast<unsigned long long>(c_look));
     atomicAdd(&sCnt[0], static_cast<unsigned long long>(lines));
     atomicAdd(&sCnt[1], static_cast<unsigned long long>(c_words));
     atomicAdd(&sCnt[2], static_cast<unsigned long long>(c_queries));

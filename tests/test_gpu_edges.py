@@ -398,6 +398,40 @@ def test_two_decoders_on_two_streams():
         r["dec"].close()
 
 
+@pytest.mark.parametrize("heavy", [0, -1])
+@pytest.mark.parametrize("beam,big", [(16, 300), (64, 800), (100, 0), (256, 300)])
+def test_many_words_completed_per_frame(beam, big, heavy):
+    """A lexicon of one-phoneme spellings with 1, 2, 3, 18 or 40 homophones and
+    nearly flat frames, so that a good part of the beam completes words in
+    every frame: words in several turns of a scoring wavefront, lookups in
+    several rounds and past the results that LDS holds (40 homophones x 4
+    sub-beams), words ranked by four lanes and by a whole wavefront.  Every
+    launch instance of the beam; the oracle's outputs."""
+    words = []
+    for ph in range(1, 21):
+        words += [(ph,)] * (1, 2, 3, 18, 40)[ph % 5]
+    lex = lexicon_from(words)
+    lm = random_small_lm(len(words), 4000)
+    B, T = 3, 16
+    lg = np.stack([peaked_logits([int(x) for x in np.random.default_rng(b).integers(0, 41, size=T)], strong=0.5,
+                                 seed=70 + b, sigma=0.7) for b in range(B)])
+    p = DecodeParams(beam=beam, subbeams=4, fusion_interval=5, fusion_top_f=beam // 2)
+    d = data_of(lex, lm, lg, p, fusion_seed=3, lengths=[T, T - 3, T])
+    say(f"[case] many words K={beam} heavy={heavy}")
+    out, dec = gpu_decode(d, params=p, lb_overrides=dict(heavy_homophones=heavy), return_decoder=True)
+    st = dec.stats()
+    dec.close()
+    assert st.word_events > st.frames * beam / 8, (st.word_events, st.frames)
+    check_parity(d, out, range(B), params=p, name=f"many-words/{beam}/{heavy}")
+    if big:
+        tile = lambda a: np.concatenate([a] * (big // B + 1))[:big]
+        db = data_of(lex, lm, tile(lg), p, fusion_seed=3, lengths=tile(d.lengths))
+        say(f"[case] many words K={beam} heavy={heavy} B={big}")
+        wide = gpu_decode(db, params=p, lb_overrides=dict(heavy_homophones=heavy))
+        for b in range(big):
+            assert wide[b][0] == out[b % B][0] and np.array_equal(wide[b][1], out[b % B][1]), b
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_random_small_lexicons_match_oracle(seed):
     """Random small lexicons over phonemes 1..5 (one to four phonemes a word,
