@@ -260,6 +260,16 @@ __device__ inline void bitonic_sort(double* sc, uint64_t* ky, uint32_t* val) {
   }
 }
 
+// Two unsigned 16-bit halves at once: bit 0 of each half of the result: the half
+// of x is below the half of y.  (A saturating difference cut to 1; as C++ the
+// compiler turns it into two compares and two selects.)
+__device__ __forceinline__ uint32_t pk_below(uint32_t x, uint32_t y) {
+  uint32_t d, r;
+  asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(d) : "v"(y), "v"(x));
+  asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(d), "v"(0x00010001));
+  return r;
+}
+
 // ------------------------------------------------------------------ n-gram tables
 
 // Looks `key` up; `lines` counts the 64-B bucket lines read.
@@ -382,12 +392,16 @@ struct Bucket {
 // (NgramTable and PresTable share the bucket layout: 16-B slots {u64 key, u32, u32})
 template <typename Table>
 __device__ __forceinline__ Bucket load_bucket(const Table& t, uint64_t bk) {
-  const uint4* line = reinterpret_cast<const uint4*>(t.slots + bk * 4);
+  // (tables are in global memory: a table pointer kept in LDS loses that, and
+  // flat loads would also wait for LDS)
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  const u4 __attribute__((address_space(1)))* line =
+      (const u4 __attribute__((address_space(1)))*)reinterpret_cast<uintptr_t>(t.slots + bk * 4);
   Bucket q;
-  q.s0 = line[0];
-  q.s1 = line[1];
-  q.s2 = line[2];
-  q.s3 = line[3];
+  q.s0 = __builtin_bit_cast(uint4, line[0]);
+  q.s1 = __builtin_bit_cast(uint4, line[1]);
+  q.s2 = __builtin_bit_cast(uint4, line[2]);
+  q.s3 = __builtin_bit_cast(uint4, line[3]);
   return q;
 }
 
@@ -547,10 +561,11 @@ __device__ __forceinline__ void emit_output(const DevParams& P, const DevState& 
 // frame:
 //   * fan-out of every hypothesis by blank, repeat and each lexicon-valid
 //     symbol (trie child mask), token / word bonuses, recombination of equal
-//     prefixes by log-sum-exp, theta pruning, top-K selection (score bins,
-//     exact rank inside the boundary bin), beam update, trie-state advance;
-//     hypothesis i is owned by LPB consecutive lanes: lane s of it handles the
-//     extensions v = 1+s, 1+s+LPB, ... and lane 0 also the merged stay;
+//     prefixes by log-sum-exp, theta pruning, top-K selection (16-bit scores
+//     in bins, exact rank around the boundary bin), beam update, trie-state
+//     advance; hypothesis i is owned by LPB consecutive lanes: lane s of it
+//     handles the extensions v = 1 + NC s .. NC (s + 1) and lane 0 also the
+//     merged stay;
 //   * Eq. (1) for the hypotheses that completed a word, by wavefronts of their
 //     own (score_words): the (word, sub-beam) pairs are grouped by (n-gram
 //     context, trie node); each group is looked up once per homophone, or, for
@@ -568,9 +583,9 @@ __device__ __forceinline__ void emit_output(const DevParams& P, const DevState& 
 // After the last frame the beam goes back to global memory, and, when out_hyps
 // is given, the workgroup also writes the stream's output (emit_output; out_fin:
 // the end of the utterance).
-// Barriers per frame: the bin range, the histogram, the bin search, the boundary
-// bin's list, the block scan, the gather, the new hypotheses (two when in
-// place), and the one that joins Eq. (1) and the next recombination.
+// Barriers per frame: the histogram, the bin search, the boundary's list, the
+// gather, the new hypotheses (two when in place), and the one that joins Eq. (1)
+// and the next recombination (the exact selection, where it is needed, has more).
 // WPE: wavefronts per SIMD the register allocation aims for (four workgroups
 // of 256 threads per CU need 4).  DB: the hypotheses are double-buffered in
 // LDS; otherwise one buffer is rewritten in place (every source entry is read
@@ -603,14 +618,10 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   static_assert(KMAX <= 256, "a hash slot holds its hypothesis in 8 bits");
   constexpr int NW = BLOCK / 64;
   constexpr int NC = (kSep + LPB - 1) / LPB;  // extension slots per lane
-  // top-K in one pass over the slots, with the bin range from bounds taken in
-  // the recombination phase, where a lane owns 5 or more slots; with fewer
-  // slots per lane a first pass for the exact range costs less than the bounds
-  constexpr bool kOnePass = NC >= 5;
-  static_assert(LPB <= 16 && LPB * NC < 64, "a lane's slots stay below symbol 64");
-  static_assert(NC + 2 < 64, "a lane's candidates (its slots, the stay and the repeat) fit the sets sel_bits and bnd");
-  // the candidate sets of a lane: 32 bits where its positions fit
-  using CandSet = typename std::conditional<(NC + 2 <= 32), uint32_t, uint64_t>::type;
+  static_assert(LPB * NC >= kSep && NC + 2 <= 32, "a lane's candidates (its slots, the stay and the repeat) fit a 32-bit set");
+  // slots in pairs (p, p + NH), 16-bit scores in the halves of a register
+  constexpr int NH = (NC + 1) / 2;
+  static_assert(NH + 1 <= 16, "the pairs' sets: 16 bits a half");
   // the wavefronts that hold the hypotheses (one thread each), and those that
   // score completed words meanwhile: the others, as many as a beam can fill
   // (every wavefront, before its other work, where none is left)
@@ -623,7 +634,8 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // against 9.80 with 512)
   constexpr int kBinBits = KMAX >= 256 ? 10 : 9;
   constexpr int kBins = 1 << kBinBits;
-  constexpr int SEL_BYTES = kBins * 4 + kBoundaryCap * 16;
+  constexpr int kBinShift = 16 - kBinBits;  // of a 16-bit score
+  constexpr int SEL_BYTES = kBoundaryCap * 20;
   constexpr int LM_BYTES = LMW * static_cast<int>(sizeof(LmWave));
   // in place: the new hypotheses' sub-beams on their way; K >= 128: the top F
   constexpr int STAGE_BYTES = DB ? 0 : 12 * KMAX * kMaxSub;
@@ -642,7 +654,14 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   __shared__ BeamLds<KMAX> sBeam[DB ? 2 : 1];
   // this frame's row and the next one's: classes 0..40; 41..63 are zero (slots past the separator)
   __shared__ double sD[2][64];
-  __shared__ double sDmax[2];  // the largest of classes 1..40
+  // the row for the 16-bit scores: Dtop, the largest of D + bonus over symbols
+  // 1..40, and every symbol's distance from it in units, 65535 at most, in the
+  // order in which the lanes own them (word ln * NH + p: slots p and p + NH)
+  __shared__ double sDtop[2];
+  // the bonus of a class (beta, gamma for the separator; 0 past it): a select
+  // between two parameters would be a load from global memory in every lane
+  __shared__ double sBonus[64];
+  __shared__ uint32_t sDq[2][LPB * NH];
   __shared__ double sAb2[KMAX], sAnb2[KMAX], sPt2[KMAX];
   __shared__ uint64_t sCut[KMAX];  // symbols whose extension went to a live hypothesis' stay
   // the prefix keys of the frame's hypotheses: inserted when the hypotheses
@@ -653,15 +672,17 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   __shared__ uint8_t sHIdx[HS];  // the slot's hypothesis (KMAX <= 256)
   // top-K selection scratch; the LM step, the fusion and the output reuse it
   __shared__ __align__(16) unsigned char sSel[UNI_BYTES];
+  __shared__ __align__(16) uint32_t sHisto[kBins];  // zero at the start of a frame
   __shared__ double sLvHi[kMaxLevels], sLvInv[kMaxLevels];
   __shared__ int32_t sLvBeta[kMaxLevels], sLvShift[kMaxLevels];
   __shared__ uint32_t sSelSrc[KMAX];
   // hypotheses that completed a word this frame: those of wavefront w from 64 w on
   __shared__ uint32_t sEvBeam[KMAX], sEvWoff[KMAX], sEvH[KMAX];
   __shared__ int32_t sEvCnt[RW];
-  __shared__ double sRed[2 * NW], sRedB[3 * NW];
+  __shared__ double sRed[2 * NW], sRedB[2 * NW];
   __shared__ int32_t sScan[NW], sScanB[NW], sScanD[NW];
-  __shared__ int32_t sBucket, sAbove, sBucketCnt, sBCount, sAthr, sNBinned;
+  __shared__ int32_t sBucket, sAbove, sBucketCnt, sBCount, sAthr, sNBinned, sTopBin;
+  __shared__ int32_t sWild;  // the last frame (tau + 1) whose scores the 16-bit ones do not describe
   // counters: probed lines, completed words, LM queries, index lines (summed over
   // the threads at the end), expansions, fused hypotheses, lookups (added by
   // thread 0 as they occur: kept here, not in every thread's registers)
@@ -684,9 +705,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     }
   };
 
-  uint32_t* const sHisto = reinterpret_cast<uint32_t*>(sSel);
-  double* const sBScore = reinterpret_cast<double*>(sSel + kBins * 4);
-  uint64_t* const sBKey = reinterpret_cast<uint64_t*>(sSel + kBins * 4 + kBoundaryCap * 8);
+  double* const sBScore = reinterpret_cast<double*>(sSel);
+  uint64_t* const sBKey = reinterpret_cast<uint64_t*>(sSel + kBoundaryCap * 8);
+  uint32_t* const sBSrc = reinterpret_cast<uint32_t*>(sSel + kBoundaryCap * 16);
   // write-back staging of the sub-beams (one-buffer instances)
   double* const sStL = reinterpret_cast<double*>(sSel);
   uint32_t* const sStH = reinterpret_cast<uint32_t*>(sStL + KMAX * kMaxSub);
@@ -749,6 +770,12 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   uint32_t arena_n = S.arena_n[b];
   int cur = 0;  // the current buffer (DB)
   for (int q = tid; q < HS; q += BLOCK) sHKey[q] = kEmptyKey;
+  for (int d = tid; d < kBins; d += BLOCK) sHisto[d] = 0;
+  for (int d = tid; d < 2 * LPB * NH; d += BLOCK) sDq[d / (LPB * NH)][d % (LPB * NH)] = 0xFFFFFFFFu;
+  if (tid == 0) {
+    sBCount = 0;
+    sWild = 0;
+  }
   // a new hypothesis' prefix key into the hash table, with its index r
   auto insert_key = [&](uint64_t key, int r) {
     uint32_t s = static_cast<uint32_t>(key) & (HS - 1);
@@ -769,6 +796,11 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       (scratch ? reinterpret_cast<QState*>(scratch + slay.off_state) : S.scrS) + static_cast<size_t>(b) * S.scap;
   uint32_t* const scrE = (scratch ? reinterpret_cast<uint32_t*>(scratch + slay.off_explicit) : S.scrE) +
                          static_cast<size_t>(b) * P.K * kMaxSub * kMaxExplicit;
+  if (tid < 64) sBonus[tid] = tid >= 1 && tid < kSep ? P.beta : (tid == kSep ? P.gamma : 0.0);
+  // units per nat of the 16-bit scores: they reach theta, at most 14, plus 2 nats
+  // down from a frame's reference (the K-th candidate lies 2 nats below the best
+  // in the middle, 10 in one frame of a hundred)
+  const double qunit = (fmin(P.theta, 14.0) + 2.0) / 65000.0, qscale = 1.0 / qunit;
   // D = alpha * log-probs of a frame into row q of sD, by one wavefront (every
   // lane): raw scores are first normalised by a log-softmax over the 41 classes
   auto set_row = [&](const DevParams& Pr, int q, float xin) {
@@ -781,22 +813,43 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     }
     const double dv = lane < kClasses ? Pr.alpha * x : 0.0;
     sD[q][lane] = dv;
-    const double dm = wave_max(lane >= 1 && lane < kClasses ? dv : kNegInf);
-    if (lane == 0) sDmax[q] = dm;
+    const bool sym = lane >= 1 && lane < kClasses;
+    const double db = dv + sBonus[lane];
+    const double top = wave_max(sym ? db : kNegInf);
+    if (lane == 0) sDtop[q] = top;
+    if (sym) {
+      const double u = (top - db) * qscale;
+      const int ln = (lane - 1) / NC, k = (lane - 1) % NC;
+      const int h = 2 * (ln * NH + (k < NH ? k : k - NH)) + (k < NH ? 0 : 1);
+      reinterpret_cast<uint16_t*>(&sDq[q][0])[h] = u < 65535.0 ? static_cast<uint16_t>(u) : uint16_t{65535};  // (also of NaN)
+    }
   };
   // the first frame's row now; in each frame the last wavefront loads the next
   // frame's row early and sets it while the first one searches the top-K's bins
   int row = 0;
+  lds_barrier();
   if (wave == 0)
     set_row(P, 0, lane < kClasses ? logits[(static_cast<size_t>(b) * Tc + tau0) * kClasses + lane] : 0.0f);
   float dnext = 0.0f;
   lds_barrier();
-  // the loaded hypotheses' keys for the first frame
+  // the loaded hypotheses' keys for the first frame, and their best total
   if (tid < n) {
     insert_key(sBeam[0].key[tid], tid);
     sCut[tid] = 0;
   }
-  lds_barrier();
+  auto best_total = [&](const BeamLds<KMAX>& H, int nh, int tid) -> double {
+    const double m = wave_max(tid < nh ? H.pt[tid] + H.Lw[tid * kMaxSub] : kNegInf);
+    if ((tid & 63) == 0) sRed[tid >> 6] = m;
+    lds_barrier();
+    double r = sRed[0];
+#pragma unroll
+    for (int w = 1; w < RW; ++w) r = fmax(r, sRed[w]);
+    return r;
+  };
+  // an upper bound of the hypotheses' totals (but for those that a word raised),
+  // and whether the next selection starts with the 16-bit scores (a full beam)
+  double btotal = best_total(sBeam[0], n, tid);
+  bool coarse = n == P.K;
   mark(kPhOther);
 
   // ---- recombination of a frame's hypotheses (buffer H, log-probs D): a
@@ -829,7 +882,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       double ext = kNegInf;
       if (par >= 0) {
         const double base = (last == static_cast<int>(H.meta[par] & 0xFF)) ? H.ab[par] : H.pt[par];
-        ext = (base + D[last]) + (last == kSep ? Pr.gamma : Pr.beta);
+        ext = (base + D[last]) + sBonus[last];
       }
       // anb2 = merge(rep, ext), then pt2 = merge(ab2, anb2); merge is
       // log-sum-exp, or max for the best-alignment recombination
@@ -1343,39 +1396,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     // the next frame's log-probs are loaded meanwhile
     if (wave == NW - 1 && lane < kClasses && more)
       dnext = logits[(static_cast<size_t>(b) * Tc + tau + 1) * kClasses + lane];
-    for (int d = tid; d < kBins; d += BLOCK) sHisto[d] = 0;
-    if (tid == 0) sBCount = 0;
     for (int s = tid; s < HS; s += BLOCK) sHKey[s] = kEmptyKey;  // for the new hypotheses' keys
-    if constexpr (kOnePass) {
-      // per wavefront: an upper bound of every candidate (sRedB[w]), the best
-      // stay (sRedB[NW + w]) and the lowest (sRedB[2 NW + w]), for the top-K's
-      // bin range (a wavefront past the last hypothesis has the neutral values
-      // without reducing)
-      if (wave * 64 < n) {
-        double st = kNegInf, up = kNegInf;
-        if (tid < n) {
-          const double lw = C.Lw[tid * kMaxSub];
-          st = sPt2[tid] + lw;
-          // no extension of this hypothesis scores above this (each of the additions
-          // rounds monotonically, base <= pt, log-prob <= sDmax, bonus <= the larger)
-          up = ((C.pt[tid] + sDmax[row]) + fmax(P.beta, P.gamma)) + lw;
-        }
-        double hi = fmax(st, up), nlo = -st;
-        wave_minmax(&hi, &nlo);
-        const double nmin = wave_max(tid < n ? -st : -HUGE_VAL);
-        if (lane == 0) {
-          sRedB[wave] = hi;
-          sRedB[NW + wave] = -nlo;
-          sRedB[2 * NW + wave] = -nmin;
-        }
-      } else if (lane == 0) {
-        sRedB[wave] = kNegInf;
-        sRedB[NW + wave] = kNegInf;
-        sRedB[2 * NW + wave] = HUGE_VAL;
-      }
-    }
-    lds_barrier();
-    mark(kPhRecomb);
     // Workgroups that share a CU: the CU's arbitration favours the older
     // wavefronts, so the workgroup dispatched second (the later half of the
     // grid, when workgroups are dispatched to the CUs in order) fell behind
@@ -1388,137 +1409,45 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       __builtin_amdgcn_s_setprio(0);
 
 
-    // ---- this lane's candidates: slot k is the extension by v = 1 + ln + LPB*k,
-    // plus the merged stay on lane 0; scores are recomputed in every pass (same
-    // operations, same result)
+    // ---- this lane's candidates: slot k is the extension by v = 1 + NC * ln + k,
+    // plus the merged stay on lane 0 and the repeat extension (the hypothesis'
+    // last symbol again, from its blank-ending part) on the lane of its symbol,
+    // whose slot is then left out of the slots, which all start from pt.  Exact
+    // scores are computed where they are needed, from LDS (same operations, same
+    // result): kept in registers across the barriers they would spill in the
+    // 128-register instances.  (A lane past the last hypothesis reads what is
+    // there and has no candidates: one round of reads, no branch.)
     const int hi_ = tid / LPB;
     const int ln = tid - hi_ * LPB;
     const bool live = hi_ < n;
-    uint64_t c_key = 0, c_rel = 0;
-    double c_stay = kNegInf, c_ab = 0.0, c_p = 0.0, c_L = 0.0;
-    int c_rep = -1;
-    if (live) {
-      c_ab = C.ab[hi_];
-      c_p = C.pt[hi_];
-      c_L = C.Lw[hi_ * kMaxSub];
-      // slot k <-> symbol 1 + ln + LPB*k: bit LPB*k of c_rel is its mask bit
-      // (slots past the separator are invalid: the mask is cut to bits 1..40,
-      // its bits 48..63 hold the node's word count)
-      c_rel = (C.tmask[hi_] & ~sCut[hi_] & ((2ull << kSep) - 1ull)) >> (1 + ln);
-      c_rep = static_cast<int>(C.meta[hi_] & 0xFF) - 1 - ln;  // LPB*k of the repeat symbol
-      c_key = C.key[hi_];
-      if (ln == 0) c_stay = sPt2[hi_] + c_L;
-    }
-    // the separator (symbol kSep = 1 + ln + LPB*k) can only be slot
-    // (kSep - 1) / LPB of lane (kSep - 1) % LPB: with k known at compile time
-    // (the unrolled slot loops) the bonus of every other slot is beta without
-    // a select
-    constexpr int kSepSlot = (kSep - 1) / LPB;
-    const bool sep_lane = ln == (kSep - 1) % LPB;
-    // (the bonuses are read once here: inside the slot loops a constant-memory
-    // load per slot would wait together with the LDS loads)
-    const double bon_ph = P.beta, bon_sep = P.gamma;
-    auto bonus_at = [&](int k) -> double { return (k == kSepSlot && sep_lane) ? bon_sep : bon_ph; };
-    // the repeat extension (the hypothesis' last symbol again, from its
-    // blank-ending part) is a candidate of its own, position NC + 1, and its
-    // slot is left out of the slot loops, whose extensions all start from pt
-    int c_rk = -1;            // its slot on this lane (-1: not on this lane, or invalid)
-    double c_rps = kNegInf;   // its score
-    if (c_rep >= 0 && c_rep % LPB == 0 && ((c_rel >> c_rep) & 1ull)) {
-      c_rk = c_rep / LPB;
-      c_rps = ((c_ab + Dc[1 + ln + c_rep]) + bonus_at(c_rk)) + c_L;
-      c_rel &= ~(1ull << c_rep);
-    }
-    auto score_now = [&](int k) -> double {
-      const bool valid = (c_rel >> (LPB * k)) & 1ull;
-      const double sc = ((c_p + Dc[1 + ln + LPB * k]) + bonus_at(k)) + c_L;
-      return valid ? sc : kNegInf;
-    };
-    auto key_of = [&](int v) -> uint64_t { return v == 0 ? c_key : prefix_step(c_key, v); };
+    const int last_ = static_cast<int>(C.meta[hi_] & 0xFF);
+    // bit k: slot k is an extension (the trie mask is cut to bits 1..40, its
+    // bits 48..63 hold the node's word count)
+    uint32_t c_val = static_cast<uint32_t>((C.tmask[hi_] & ~sCut[hi_] & ((2ull << kSep) - 1ull)) >> (1 + NC * ln)) & ((1u << NC) - 1u);
+    c_val = live ? c_val : 0u;
+    const int rk = last_ - 1 - NC * ln;
+    const uint32_t rbit = static_cast<unsigned>(rk) < static_cast<unsigned>(NC) ? 1u << (rk & 31) : 0u;
+    const bool stays = live && ln == 0, reps = (c_val & rbit) != 0;
+    c_val &= ~rbit;
     // position k of the lane: slot k (k < NC), the stay (NC), the repeat (NC + 1)
-    auto pos_v = [&](int k) -> int { return k == NC ? 0 : 1 + ln + LPB * (k == NC + 1 ? c_rk : k); };
-    auto pos_score = [&](int k) -> double { return k == NC ? c_stay : (k == NC + 1 ? c_rps : score_now(k)); };
-
-    // ---- top-K and the theta cut.  Level 0 bins the candidates at or above L0
-    // by (U - score) over [L0, U] into kBins, where U is at least every
-    // candidate's score and L0 at most every candidate that can be selected:
-    // at most the cut (best - theta) or at most the K-th candidate (with a
-    // full beam the K stays are candidates, so the K-th candidate scores at
-    // least the lowest stay).  The map is monotone, so bins above the one
-    // holding the K-th candidate are taken whole, and the bins above the
-    // cut's bin hold only candidates above the cut.  U and L0 come from the
-    // recombination phase's bounds (U: the stays and each hypothesis'
-    // extension bound; L0: the best stay - theta, or the lowest stay if the
-    // beam is full and that is higher), so one pass over the slots bins them;
-    // the exact best is taken only where the cut might bind (below), and then
-    // the members of the cut's bin are tested against the cut exactly.
-    // Without a finite stay (and in the instances without bounds) a first
-    // pass finds best and the lowest candidate: U = best, L0 = max(best -
-    // theta, lowest).  The bin holding the K-th candidate is resolved exactly
-    // by rank on (score desc, key asc) when it holds at most kBoundaryCap
-    // candidates; otherwise it is re-binned over its own score range (deeper
-    // levels), and when its scores are all equal, by the bits of the key
-    // (smaller key first).
-    const double theta = P.theta;
-    double U = kNegInf, Bst = kNegInf, Smin = kNegInf;
-    if constexpr (kOnePass) {
-      U = sRedB[0];
-      Bst = sRedB[NW];
-      Smin = sRedB[2 * NW];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) {
-        U = fmax(U, sRedB[w]);
-        Bst = fmax(Bst, sRedB[NW + w]);
-        Smin = fmin(Smin, sRedB[2 * NW + w]);
-      }
-    }
-    double L0 = Bst - theta;
-    if (n >= P.K) L0 = fmax(L0, Smin);  // (a stay of -inf leaves Smin at -inf)
-    // with a first pass the best is exact before the binning (and every binned
-    // candidate is at or above the cut)
-    const bool first_pass = Bst == kNegInf;  // no bounds, or no finite stay (uniform)
-    double best = kNegInf;
-    if (first_pass) {
-      double mx = fmax(c_stay, c_rps);
-      double mn = fmin(c_stay != kNegInf ? c_stay : HUGE_VAL, c_rps != kNegInf ? c_rps : HUGE_VAL);
-#pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        const double sc = score_now(k);
-        mx = fmax(mx, sc);
-        mn = fmin(mn, sc != kNegInf ? sc : HUGE_VAL);
-      }
-      double lowest;
-      block_minmax<BLOCK, false>(mx, mn, sRed, &best, &lowest);
-      U = best;
-      L0 = fmax(best - theta, lowest);
-    }
-    const double inv0 = U > L0 ? static_cast<double>(kBins) / (U - L0) : 0.0;
-    const int shift0 = U > L0 ? -1 : 64 - kBinBits;
-    auto bin_score = [&](double hi, double inv, double s) -> int {
-      const double x = (hi - s) * inv;
-      return x >= static_cast<double>(kBins - 1) ? kBins - 1 : static_cast<int>(x);
+    auto pos_v = [&](int k) -> int {
+      const int v = k == NC + 1 ? last_ : 1 + NC * ln + k;
+      return k == NC ? 0 : v;
     };
-    // level 0: (U - s) * inv0 as one fused multiply-add of s, clamped to the
-    // bins; each step rounds monotonically, so a higher score never takes a
-    // higher bin (U bounds every candidate, so the value is at least about 0)
-    const double ninv0 = -inv0, uinv0 = U * inv0;
-    auto bin_lv0 = [&](double s) -> int {
-      return static_cast<int>(fmax(fmin(fma(s, ninv0, uinv0), static_cast<double>(kBins - 1)), 0.0));
+    auto pos_score = [&](int k) -> double {
+      const double* const b = k == NC ? sPt2 : (k == NC + 1 ? C.ab : C.pt);
+      const int x = k == NC ? kClasses : pos_v(k);  // (class 41: nothing added, no bonus)
+      return ((b[hi_] + Dc[x]) + sBonus[x]) + C.Lw[hi_ * kMaxSub];
     };
-    auto bin0 = [&](int v, double s) -> int {
-      return shift0 < 0 ? bin_lv0(s) : static_cast<int>((key_of(v) >> shift0) & (kBins - 1));
-    };
-    // deeper levels (rare): parameters in LDS
-    auto bin_at = [&](int l, int v, double s) -> int {
-      const int sh = sLvShift[l];
-      if (sh >= 0) return static_cast<int>((key_of(v) >> sh) & (kBins - 1));
-      return bin_score(sLvHi[l], sLvInv[l], s);
+    auto key_of = [&](int v) -> uint64_t {
+      const uint64_t k = C.key[hi_];
+      return v == 0 ? k : prefix_step(k, v);
     };
     // finds the bin holding the need-th candidate of sHisto (sBucket, sAbove,
-    // sBucketCnt) and, for bthr < kBins, the number of candidates in the bins
-    // above bin bthr (sAthr); returns the number of binned candidates.  The
-    // first wavefront scans the bins, kBins / 64 per lane, so one barrier ends it.
-    auto find_bin = [&](int need_in, int bthr) -> int {
+    // sBucketCnt) and a bin that no candidate lies above (sTopBin); returns the
+    // number of binned candidates.  The first wavefront scans the bins, kBins /
+    // 64 per lane, so one barrier ends it.
+    auto find_bin = [&](int need_in) -> int {
       constexpr int PERW = kBins / 64;
       static_assert(PERW % 4 == 0, "bins per lane in 16-B loads");
       if (wave == 0) {
@@ -1537,8 +1466,12 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         for (int q = 0; q < PERW; ++q) local += h[q];
         const int incl = wave_scan_incl(local);
         const int before = incl - local;
-        if (lane == 63) sNBinned = incl;
-        if (need_in > 0 && before < need_in && incl >= need_in) {
+        const uint64_t some = __ballot(local > 0);
+        if (lane == 63) {
+          sNBinned = incl;
+          sTopBin = some ? __builtin_ctzll(some) * PERW : 0;
+        }
+        if (before < need_in && incl >= need_in) {
           int acc = before;
           bool found = false;
 #pragma unroll
@@ -1552,56 +1485,226 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
             acc += h[q];
           }
         }
-        if (bthr < kBins && lane == bthr / PERW) {
-          int acc = before;
-#pragma unroll
-          for (int q = 0; q < PERW; ++q) acc += (lane * PERW + q < bthr) ? h[q] : 0;
-          sAthr = acc;
-        }
       }
       lds_barrier();
       return sNBinned;
     };
+    const double theta = P.theta;
+    int nsel = 0;
+    bool done = false;
 
+    // ---- top-K by 16-bit scores: a candidate's distance below a reference, in
+    // units of 1 / qscale nat, as the sum of its hypothesis' and its symbol's,
+    // both rounded down -- two slots in one saturating packed addition, where
+    // the 64-bit score and its bin took a dozen instructions per slot and first
+    // needed the range of the scores, a reduction over the workgroup.  (With
+    // it, and everything read from LDS without branches, the frame's top-K went
+    // from 14.7 k to 10.5 k cycles at K = 256, 7.6 k to 6.2 k at K = 32; 512 x
+    // 500 frames at K = 256 7.39 -> 5.86 ms, 256 x 500 at K = 64 4.17 -> 3.62.)
+    // The distance is at
+    // most 2 units above the 16-bit score (and less than one more for the
+    // rounding of the 64-bit sums, all below 1e9 here).  So with the K-th
+    // candidate in bin b of 2^kBinShift units, every candidate 3 units before
+    // the bin is selected, none 3 units past it is, and those between, ranked
+    // exactly by (score desc, key asc), fill the rest.
+    // The reference bounds every candidate from above: the beam's best total
+    // plus the best that this frame can add (its blank, or its best symbol with
+    // its bonus, and log 3 for the paths that a stay sums).  Where it does not
+    // (a word raised a hypothesis; scores of 1e9), where fewer than K candidates
+    // are within the 16 bits, where theta may cut or the bin is crowded, the
+    // exact selection below takes the frame.
+    double ref = 0.0;
+    if (coarse) {
+      ref = btotal + (fmax(sDtop[row], Dc[0]) + 1.2);
+      done = fabs(ref) < 1e9;
+    }
+    if (done) {
+      typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+      constexpr int NP = NH + 1;  // the pairs of slots, and (stay, repeat)
+      const double p = C.pt[hi_], lw = C.Lw[hi_ * kMaxSub], dtop = sDtop[row];
+      const double sc_s = sPt2[hi_] + lw;
+      const double sc_r = ((C.ab[hi_] + Dc[last_]) + sBonus[last_]) + lw;
+      const double base = (p + lw) + dtop;
+      us2 q2[NP];
+#pragma unroll
+      for (int w = 0; w < NH; ++w) q2[w] = __builtin_bit_cast(us2, sDq[row][ln * NH + w]);
+      auto units = [&](double sc) -> uint32_t { return static_cast<uint32_t>(fmin(fmax((ref - sc) * qscale, 0.0), 65535.0)); };
+      const uint32_t bq = units(base), qs = units(sc_s), qr = units(sc_r);
+      const bool wild = !(fabs(p) < 1e9 && fabs(lw) < 1e9 && base <= ref) || (stays && !(sc_s <= ref)) || (reps && !(sc_r <= ref));
+      if (live && wild) sWild = tau + 1;
+      const us2 b2 = __builtin_bit_cast(us2, bq | (bq << 16));
+#pragma unroll
+      for (int w = 0; w < NH; ++w) q2[w] = __builtin_elementwise_add_sat(b2, q2[w]);
+      q2[NH] = __builtin_bit_cast(us2, qs | (qr << 16));
+      // the candidates as bits in the pairs' order: slot w at bit w, slot w + NH
+      // at bit 16 + w, the stay at bit NH, the repeat at bit 16 + NH
+      const uint32_t vbits = (c_val & ((1u << NH) - 1u)) | ((c_val >> NH) << 16) | (stays ? 1u << NH : 0u) |
+                             (reps ? 1u << (16 + NH) : 0u);
+      // (what lies past the 16 bits counts in the last bin, which is never used)
+#pragma unroll
+      for (int w = 0; w < NP; ++w) {
+        const uint32_t x = __builtin_bit_cast(uint32_t, q2[w]);
+        if (vbits & (1u << w)) atomicAdd(&sHisto[(x & 0xFFFFu) >> kBinShift], 1u);
+        if (w == NH || w + NH < NC) {
+          if (vbits & (1u << (16 + w))) atomicAdd(&sHisto[x >> (16 + kBinShift)], 1u);
+        }
+      }
+      lds_barrier();
+      if (wave == NW - 1 && more) set_row(P, row ^ 1, dnext);
+      const int binned = find_bin(P.K);
+      const int bk = sBucket;
+      // no candidate scores above top, the K-th at least low
+      const double top = ref - static_cast<double>(sTopBin << kBinShift) * qunit;
+      const double low = ref - static_cast<double>(((bk + 1) << kBinShift) + 4) * qunit;
+      done = binned >= P.K && bk < kBins - 1 && sWild != tau + 1 && low >= top - theta;
+      if (done) {
+        const int ta = (bk << kBinShift) - 3;         // selected: below ta
+        const int tb = ((bk + 1) << kBinShift) + 3;   // not selected: tb and above
+        const uint32_t ua = static_cast<uint32_t>(ta < 0 ? 0 : ta), ub = static_cast<uint32_t>(tb);
+        const uint32_t a2 = ua | (ua << 16), c2 = ub | (ub << 16);
+        uint32_t sel = 0, amb = 0;
+#pragma unroll
+        for (int w = 0; w < NP; ++w) {
+          sel |= pk_below(__builtin_bit_cast(uint32_t, q2[w]), a2) << w;
+          amb |= pk_below(__builtin_bit_cast(uint32_t, q2[w]), c2) << w;
+        }
+        sel &= vbits;
+        amb &= vbits & ~sel;
+        // set bit -> position of the lane
+        auto pos_of = [&](int bit) -> int {
+          const int w = bit & 15, h = bit >> 4;
+          return w == NH ? NC + h : w + h * NH;
+        };
+        const int cnt = __popc(sel);
+        const int incl = wave_scan_incl(cnt);
+        if (lane == 63) sScanB[wave] = incl;
+#pragma unroll 1
+        for (uint32_t m = amb; m; m &= m - 1) {
+          const int k = pos_of(__ffs(m) - 1);
+          const int v = pos_v(k);
+          const double sc = pos_score(k);
+          const uint64_t key = key_of(v);
+          const int slot = atomicAdd(&sBCount, 1);
+          if (slot < kBoundaryCap) {
+            sBScore[slot] = sc;
+            sBKey[slot] = key;
+            sBSrc[slot] = static_cast<uint32_t>(hi_) | (static_cast<uint32_t>(v) << 16);
+          }
+        }
+        lds_barrier();
+        int wpos = incl - cnt, nsure = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          const int c = sScanB[w];
+          wpos += w < wave ? c : 0;
+          nsure += c;
+        }
+        const int nbc = sBCount;
+        const int need = P.K - nsure;
+        done = nbc <= kBoundaryCap && need >= 0 && need <= nbc;
+        if (done) {
+#pragma unroll 1
+          for (uint32_t m = sel; m; m &= m - 1) {
+            const uint32_t v = static_cast<uint32_t>(pos_v(pos_of(__ffs(m) - 1)));
+            sSelSrc[wpos++] = static_cast<uint32_t>(hi_) | (v << 16);
+          }
+          // eight lanes per candidate of the list share the count of those that
+          // rank before it
+          for (int m = tid >> 3; m < nbc; m += BLOCK / 8) {
+            const double sc = sBScore[m];
+            const uint64_t key = sBKey[m];
+            int rank = 0;
+            for (int u = tid & 7; u < nbc; u += 8) {
+              const double su = sBScore[u];
+              const uint64_t ku = sBKey[u];
+              rank += (su > sc || (su == sc && ku < key)) ? 1 : 0;
+            }
+            rank += dpp_i32<kDppXor1>(rank, 0);
+            rank += dpp_i32<kDppXor2>(rank, 0);
+            rank += dpp_i32<kDppHalfMirror>(rank, 0);
+            if ((tid & 7) == 0 && rank < need) sSelSrc[nsure + rank] = sBSrc[m];
+          }
+          nsel = P.K;
+          btotal = top;
+        }
+      }
+    } else {
+      if (wave == NW - 1 && more) set_row(P, row ^ 1, dnext);
+    }
+    if (!done) {
+    // ---- top-K and the theta cut, exactly.  A first pass finds the best and the
+    // lowest candidate; level 0 bins the candidates within theta of the best by
+    // (best - score) into kBins; the map is monotone, so bins above the one
+    // holding the K-th candidate are taken whole.  That bin is resolved exactly
+    // by rank on (score desc, key asc) when it holds at most kBoundaryCap
+    // candidates; otherwise it is re-binned over its own score range (deeper
+    // levels), and when its scores are all equal, by the bits of the key
+    // (smaller key first).
+    lds_barrier();  // the coarse selection's reads are done
+    for (int d = tid; d < kBins; d += BLOCK) sHisto[d] = 0;
+    if (tid == 0) sBCount = 0;
+    double best;
+    double c_p = kNegInf, c_L = 0.0, c_stay = kNegInf, c_rps = kNegInf;
+    if (live) {
+      c_p = C.pt[hi_];
+      c_L = C.Lw[hi_ * kMaxSub];
+      if (stays) c_stay = pos_score(NC);
+      if (reps) c_rps = pos_score(NC + 1);
+    }
+    // the separator can only be slot (kSep - 1) % NC of lane (kSep - 1) / NC
+    const double bon_ph = P.beta, bon_sep = P.gamma;
+    auto score_now = [&](int k) -> double {
+      const bool sep = k == (kSep - 1) % NC && ln == (kSep - 1) / NC;
+      const double sc = ((c_p + Dc[1 + NC * ln + k]) + (sep ? bon_sep : bon_ph)) + c_L;
+      return ((c_val >> k) & 1u) ? sc : kNegInf;
+    };
+    double mx = fmax(c_stay, c_rps);
+    double mn = fmin(c_stay != kNegInf ? c_stay : HUGE_VAL, c_rps != kNegInf ? c_rps : HUGE_VAL);
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      const double sc = score_now(k);
+      mx = fmax(mx, sc);
+      mn = fmin(mn, sc != kNegInf ? sc : HUGE_VAL);
+    }
+    double lowest;
+    block_minmax<BLOCK, false>(mx, mn, sRed, &best, &lowest);
+    const double U = best, L0 = fmax(best - theta, lowest);
+    const double inv0 = U > L0 ? static_cast<double>(kBins) / (U - L0) : 0.0;
+    const int shift0 = U > L0 ? -1 : 64 - kBinBits;
+    auto bin_score = [&](double hi, double inv, double s) -> int {
+      const double x = (hi - s) * inv;
+      return x >= static_cast<double>(kBins - 1) ? kBins - 1 : static_cast<int>(x);
+    };
+    // level 0: (U - s) * inv0 as one fused multiply-add of s, clamped to the
+    // bins; each step rounds monotonically, so a higher score never takes a
+    // higher bin
+    const double ninv0 = -inv0, uinv0 = U * inv0;
+    auto bin_lv0 = [&](double s) -> int {
+      return static_cast<int>(fmax(fmin(fma(s, ninv0, uinv0), static_cast<double>(kBins - 1)), 0.0));
+    };
+    auto bin0 = [&](int v, double s) -> int {
+      return shift0 < 0 ? bin_lv0(s) : static_cast<int>((key_of(v) >> shift0) & (kBins - 1));
+    };
+    // deeper levels (rare): parameters in LDS
+    auto bin_at = [&](int l, int v, double s) -> int {
+      const int sh = sLvShift[l];
+      if (sh >= 0) return static_cast<int>((key_of(v) >> sh) & (kBins - 1));
+      return bin_score(sLvHi[l], sLvInv[l], s);
+    };
     // level-0 bin of each of the lane's candidates, kept packed 16 bits per slot
     // (0xFFFF: no candidate); exact scores are recomputed only inside the boundary bin
     uint32_t binp[(NC + 1) / 2];
-    // (with several lanes per hypothesis the candidates' inputs are made opaque
-    // here so that their scores are recomputed below instead of being kept live
-    // across the block reduction; the one-lane instance has the registers)
-    if constexpr (LPB > 1) asm volatile("" : "+v"(c_ab), "+v"(c_p), "+v"(c_L), "+v"(c_rel), "+v"(c_key));
     uint32_t bin_stay = 0xFFFFu, bin_rep = 0xFFFFu;
     if (c_stay >= L0) bin_stay = static_cast<uint32_t>(bin0(0, c_stay));  // (-inf: no stay)
     if (c_rps >= L0) bin_rep = static_cast<uint32_t>(bin0(pos_v(NC + 1), c_rps));
-    // the bins first, then the histogram: with no LDS write among them, the
-    // slots' log-prob loads are issued together instead of each waiting behind
-    // the previous slot's atomic
-    if (shift0 < 0) {
 #pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        // branch-free: the score and bin of the slot, valid or not (a bin in
-        // range either way), then a select
-        const bool valid = (c_rel >> (LPB * k)) & 1ull;
-        const double sc = ((c_p + Dc[1 + ln + LPB * k]) + bonus_at(k)) + c_L;
-        const bool in = valid && sc >= L0;
-        const uint32_t bn = in ? static_cast<uint32_t>(bin_lv0(sc)) : 0xFFFFu;
-        if (k & 1)
-          binp[k >> 1] |= bn << 16;
-        else
-          binp[k >> 1] = bn;
-      }
-    } else {
-      // every candidate in range has the same score: bins by key bits
-#pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        const double sc = score_now(k);
-        const bool in = sc >= L0;
-        const uint32_t bn = in ? static_cast<uint32_t>(bin0(1 + ln + LPB * k, sc)) : 0xFFFFu;
-        if (k & 1)
-          binp[k >> 1] |= bn << 16;
-        else
-          binp[k >> 1] = bn;
-      }
+    for (int k = 0; k < NC; ++k) {
+      const double sc = score_now(k);
+      const uint32_t bn = sc >= L0 ? static_cast<uint32_t>(bin0(1 + NC * ln + k, sc)) : 0xFFFFu;
+      if (k & 1)
+        binp[k >> 1] |= bn << 16;
+      else
+        binp[k >> 1] = bn;
     }
     if (bin_stay != 0xFFFFu) atomicAdd(&sHisto[bin_stay], 1u);
     if (bin_rep != 0xFFFFu) atomicAdd(&sHisto[bin_rep], 1u);
@@ -1611,108 +1714,33 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       if (bn != 0xFFFFu) atomicAdd(&sHisto[bn], 1u);
     }
     lds_barrier();
-    if (wave == NW - 1 && more) set_row(P, row ^ 1, dnext);
-    // With bounds, the exact best is needed only if the K-th candidate may lie
-    // at or below U - theta (>= best - theta): when it lies in a bin above that
-    // value's, every candidate up to it is above the cut, which cannot bind.
-    int nbinned = 0, bthr = kBins;
-    bool exact_cut = first_pass;
-    if (!first_pass) {
-      const double thr_hi = U - theta;
-      const int bhi = (shift0 < 0 && thr_hi > L0) ? bin_lv0(thr_hi) : kBins;
-      nbinned = find_bin(P.K, kBins);
-      if (!(nbinned >= P.K && sBucket < bhi)) {
-        double mx = fmax(c_stay, c_rps);
-#pragma unroll
-        for (int k = 0; k < NC; ++k) mx = fmax(mx, score_now(k));
-        best = block_max<BLOCK>(mx, sRed);
-        exact_cut = true;
-      }
-    }
-    const double thr = best - theta;  // (read only with exact_cut)
-    if (exact_cut) {
-      // the cut's bin (kBins: every binned candidate is at or above the cut)
-      bthr = (shift0 < 0 && thr > L0) ? bin_lv0(thr) : kBins;
-      nbinned = find_bin(P.K, bthr);
-    }
-    // three cases: the K-th candidate lies above the cut's bin (resolve its
-    // bin); every candidate is selected; or the cut's bin decides (its members
-    // at or above the cut, as many as are still needed)
+    const int nbinned = find_bin(P.K);
+    // the K-th candidate's bin is resolved, or every binned candidate is selected
     int beta0 = kBins, nlev = 1, need = 0, nbc = 0, cntb = 0;
-    bool all_bin = false, resolve = false, cutbin = false;
-    if (nbinned >= P.K && sBucket < bthr) {
+    bool all_bin = false;
+    const bool resolve = nbinned >= P.K;
+    if (resolve) {
       beta0 = sBucket;
       need = P.K - sAbove;
       cntb = sBucketCnt;
-      resolve = true;
-    } else if (bthr < kBins) {
-      beta0 = bthr;
-      need = P.K - sAthr;
-      cutbin = true;
     }
     // level 0 decides every candidate outside the boundary bin: above it taken,
-    // below it dropped; bnd marks this lane's candidates inside it (bit k: slot
-    // k, bit NC: the stay)
-    CandSet sel_bits = 0;  // bit 0: the stay, bit k+1: slot k
-    CandSet bnd = 0;
-    // lowest set bit and population count of a candidate set
-    auto set_ffs = [](CandSet m) -> int {
-      if constexpr (sizeof(CandSet) == 4) return __ffs(m) - 1;
-      else return __ffsll(static_cast<unsigned long long>(m)) - 1;
+    // below it dropped; bnd marks this lane's candidates inside it
+    uint32_t sel_bits = 0, bnd = 0;  // bit k: position k
+    auto classify = [&](uint32_t bn, int bit) {
+      sel_bits |= static_cast<uint32_t>(static_cast<int>(bn) < beta0) << bit;
+      bnd |= static_cast<uint32_t>(static_cast<int>(bn) == beta0) << bit;
     };
-    auto set_popc = [](CandSet m) -> int {
-      if constexpr (sizeof(CandSet) == 4) return __popc(m);
-      else return __popcll(m);
-    };
-    // (branch-free: 0xFFFF, no candidate, is above every bin index; the two
-    // sets are updated separately so that they stay in registers)
-    auto classify = [&](uint32_t bn, int bit, int bbit) {
-      sel_bits |= static_cast<CandSet>(static_cast<int>(bn) < beta0) << bit;
-      bnd |= static_cast<CandSet>(static_cast<int>(bn) == beta0) << bbit;
-    };
-    classify(bin_stay, 0, NC);
-    classify(bin_rep, NC + 1, NC + 1);
+    classify(bin_stay, NC);
+    classify(bin_rep, NC + 1);
 #pragma unroll
-    for (int k = 0; k < NC; ++k) classify((binp[k >> 1] >> ((k & 1) * 16)) & 0xFFFFu, k + 1, k);
-    if (cutbin) {
-      // the cut's bin: members below the cut are no candidates.  When the bin
-      // is small (the usual case) its members at or above the cut go straight
-      // to the exact rank, whose list also counts them; otherwise they are
-      // counted first and the bin is refined like any boundary bin.
-      const bool small = static_cast<int>(sHisto[bthr]) <= kBoundaryCap;  // (uniform)
-#pragma unroll 1
-      for (CandSet m = bnd; m; m &= m - 1) {
-        const int k = set_ffs(m);
-        const double sc = pos_score(k);
-        if (!(sc >= thr)) {
-          bnd &= ~(CandSet{1} << k);
-        } else if (small) {
-          const int slot = atomicAdd(&sBCount, 1);
-          sBScore[slot] = sc;
-          sBKey[slot] = key_of(pos_v(k));
-        }
-      }
-      if (small) {
-        lds_barrier();
-        nbc = sBCount;
-        cntb = nbc;
-        all_bin = cntb <= need;  // else: ranked exactly below
-      } else {
-        int cnt = 0;
-        (void)block_scan<BLOCK>(set_popc(bnd), sScanD, &cnt);
-        cntb = cnt;
-        if (cntb <= need)
-          all_bin = true;
-        else
-          resolve = true;
-      }
-    }
+    for (int k = 0; k < NC; ++k) classify((binp[k >> 1] >> ((k & 1) * 16)) & 0xFFFFu, k);
     // the lane's boundary-bin candidates (v, exact score) that also lie in the
     // boundary bins of levels 1..L-1
     auto for_bnd = [&](int L, auto&& f) {
 #pragma unroll 1
-      for (CandSet m = bnd; m; m &= m - 1) {
-        const int k = set_ffs(m);
+      for (uint32_t m = bnd; m; m &= m - 1) {
+        const int k = __ffs(m) - 1;
         const int v = pos_v(k);
         const double sc = pos_score(k);
         bool in = true;
@@ -1746,7 +1774,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         if (key_level) key_shift -= kBinBits;
         for_bnd(L, [&](int, int v, double sc) { atomicAdd(&sHisto[bin_at(L, v, sc)], 1u); });
         lds_barrier();
-        (void)find_bin(need, kBins);
+        (void)find_bin(need);
         if (tid == 0) sLvBeta[L] = sBucket;
         need -= sAbove;
         cntb = sBucketCnt;
@@ -1756,8 +1784,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       if (cntb == need) {
         all_bin = true;
       } else {
-        // exact rank inside the boundary bin (a flat key level of shift 0 holds one
-        // key); sBCount was cleared at the start of the frame
+        // exact rank inside the boundary bin (a flat key level of shift 0 holds one key)
         for_bnd(nlev, [&](int, int v, double sc) {
           const int slot = atomicAdd(&sBCount, 1);
           if (slot < kBoundaryCap) {
@@ -1773,8 +1800,8 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     // the boundary bin's candidates: the deeper levels, then the exact rank on
     // (score desc, key asc)
 #pragma unroll 1
-    for (CandSet m = bnd; m; m &= m - 1) {
-      const int k = set_ffs(m);
+    for (uint32_t m = bnd; m; m &= m - 1) {
+      const int k = __ffs(m) - 1;
       const int v = pos_v(k);
       const double sc = pos_score(k);
       bool take = true;
@@ -1792,25 +1819,29 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         for (int u = 0; u < nbc; ++u) rank += ranks_before(sBScore[u], sBKey[u], sc, key);
         take = rank < need;
       }
-      if (take) sel_bits |= CandSet{1} << (k == NC ? 0 : (k == NC + 1 ? NC + 1 : k + 1));
+      if (take) sel_bits |= 1u << k;
     }
-    int nsel = 0;
-    int wpos = block_scan<BLOCK, false>(set_popc(sel_bits), sScanB, &nsel);
+    int wpos = block_scan<BLOCK, false>(__popc(sel_bits), sScanD, &nsel);
     if (nsel > P.K) {  // cannot happen when the selection is exact; never write past K entries
       nsel = P.K;
       if (tid == 0) atomicOr(S.flags, kFlagSelect);
     }
 #pragma unroll 1
-    for (CandSet m = sel_bits; m && wpos < nsel; m &= m - 1) {
-      const int bit = set_ffs(m);
-      const uint32_t v = static_cast<uint32_t>(pos_v(bit == 0 ? NC : (bit == NC + 1 ? NC + 1 : bit - 1)));
+    for (uint32_t m = sel_bits; m && wpos < nsel; m &= m - 1) {
+      const uint32_t v = static_cast<uint32_t>(pos_v(__ffs(m) - 1));
       sSelSrc[wpos++] = static_cast<uint32_t>(hi_) | (v << 16);
+    }
+    btotal = best;
+    coarse = nsel == P.K;
     }
     lds_barrier();
     mark(kPhTopK);
 
     // ---- the new hypotheses; an extension's trie node is fetched now and
-    // stored after the next frame's recombination
+    // stored after the next frame's recombination.  (The next selection's bins
+    // are cleared meanwhile.)
+    for (int d = tid; d < kBins; d += BLOCK) sHisto[d] = 0;
+    if (tid == 0) sBCount = 0;
     const int r = tid;
     int is_event = 0;
     uint32_t ev_woff = 0, ev_H = 0;
@@ -1839,7 +1870,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       } else {
         const int last = meta_i & 0xFF;
         const double base = (v == last) ? C.ab[i] : C.pt[i];
-        const double anb = (base + Dc[v]) + (v == kSep ? P.gamma : P.beta);
+        const double anb = (base + Dc[v]) + sBonus[v];
         const uint64_t tm = C.tmask[i];
         w_key = prefix_step(C.key[i], v);
         w_pkey = C.key[i];
@@ -2109,8 +2140,12 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           }
         }
       }
-      if (tid == 0) sCnt[5] += static_cast<unsigned long long>(F);
+      if (tid == 0) {
+        sCnt[5] += static_cast<unsigned long long>(F);
+        sBCount = 0;
+      }
       lds_barrier();
+      btotal = best_total(N, n, tid);
       mark(kPhFusion);
     }
     if constexpr (DB) cur ^= 1;

@@ -398,6 +398,59 @@ def test_two_decoders_on_two_streams():
         r["dec"].close()
 
 
+SELECTION_CASES = {
+    # what the 16-bit scores of the top-K have to leave to the exact selection, or describe at their limits
+    "masked": dict(mask=-np.inf),                      # classes that no path may take
+    "lowest": dict(mask=float(np.finfo(np.float32).min)),  # the same as the type's lowest value
+    "steep": dict(alpha=1e8, theta=1e30),                          # totals past 1e9
+    "raised": dict(omega=-1.5),                        # a completed word raises its hypothesis
+    "bonuses": dict(beta=60.0, gamma=-40.0),           # far apart, and a separator below every phoneme
+    "far": dict(alpha=6.0, theta=1e30),                # candidates many times 16 nats below the best
+    "near": dict(alpha=0.01, theta=0.5),               # a cut that binds among close scores
+    "edge": dict(alpha=2.0, theta=14.0),               # a cut near the end of the 16 bits
+}
+
+
+@pytest.mark.parametrize("beam,big", [(8, 300), (32, 300), (64, 800), (128, 0), (256, 300)])
+@pytest.mark.parametrize("case", sorted(SELECTION_CASES))
+def test_selection_by_coarse_scores(case, beam, big):
+    """The top-K's 16-bit scores at their limits and past them, in every launch
+    instance: the oracle's beams."""
+    kw = dict(SELECTION_CASES[case])
+    mask = kw.pop("mask", None)
+    src = load_workload("t-c20k", batch=3)
+    T = 48
+    lg = np.array(src.logits[:, :T])
+    if mask is not None:
+        rng = np.random.default_rng(5)
+        for b in range(lg.shape[0]):
+            for t in range(T):
+                low = rng.permutation(np.argsort(lg[b, t])[:36])[:25]
+                lg[b, t, low[low > 0]] = mask
+    p = DecodeParams(**{**src.workload.params.__dict__, "beam": beam, "fusion_interval": 7, "fusion_top_f": beam // 3, **kw})
+    lengths = [T, T - 5, T - 11]
+    d = data_of(src.lexicon, src.lm, lg, p, fusion_seed=src.fusion_seed, lengths=lengths)
+    say(f"[case] selection {case} K={beam}")
+    out = gpu_decode(d, params=p)
+    # (totals of 1e9 are given out in 32 bits: compared relative to their size)
+    if case == "steep":
+        import oracle
+        orc, op = oracle.Oracle(d.lexicon, d.lm), oracle.params_from(p, fusion_seed=d.fusion_seed)
+        for b in range(3):
+            r = orc.decode(lg[b, :lengths[b]], op)
+            assert [list(w) for w in out[b][0]] == [[int(x) for x in w] for w in r.words]
+            assert np.allclose(out[b][1], np.array(r.total), rtol=1e-6, atol=0)
+    else:
+        check_parity(d, out, range(3), params=p, name=f"selection/{case}/{beam}")
+    if big:
+        tile = lambda a: np.concatenate([a] * (big // 3 + 1))[:big]
+        db = data_of(src.lexicon, src.lm, tile(lg), p, fusion_seed=src.fusion_seed, lengths=tile(d.lengths))
+        say(f"[case] selection {case} K={beam} B={big}")
+        wide = gpu_decode(db, params=p)
+        for b in range(big):
+            assert wide[b][0] == out[b % 3][0] and np.array_equal(wide[b][1], out[b % 3][1]), b
+
+
 @pytest.mark.parametrize("heavy", [0, -1])
 @pytest.mark.parametrize("beam,big", [(16, 300), (64, 800), (100, 0), (256, 300)])
 def test_many_words_completed_per_frame(beam, big, heavy):
