@@ -151,11 +151,10 @@ typedef struct lb_stats {
   int64_t probe_lines;  /* 64-B hash-table lines read by the LM lookups (n-gram
                            tables and the explicit-continuation index)           */
   int64_t lm_lookups;   /* n-gram lookups done: one per distinct (context, word)
-                           among the queries of a stream-frame that one wavefront
-                           scores (up to 4 completed words, more where many are
-                           completed), except homophones of heavy nodes that the
-                           continuation index shows to back off to their unigram
-                           (scored without a lookup)                            */
+                           among the queries of a completed word's sub-beams,
+                           except homophones of heavy nodes that the continuation
+                           index shows to back off to their unigram (scored
+                           without a lookup)                                    */
   int64_t launches[8];  /* kernel launches: [0] decode (all frames of a call), [1]
                            output, [2] external-fusion select, [3] export, [4]
                            apply, [5] stream reset, [6..7] unused                */

@@ -524,6 +524,7 @@ __device__ __forceinline__ unsigned long long group_key(const Ctx& ctx, uint32_t
 // to which a fully looked-up group is ranked by one lane.
 constexpr int kWaveWords = 64 / kMaxSub;
 constexpr int kWaveTasks = 16;
+constexpr uint32_t kTopWords = 4;  // of a heavy word, read ahead in unigram order (o + 1 decide it, o <= 3)
 constexpr int kLmRes = 64;
 constexpr uint32_t kLaneMaxH = 16;
 struct LmWave {
@@ -904,12 +905,14 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     }
   };
 
+  // (where the registers allow: read ahead what the ranking may need)
+  constexpr bool kAhead = WPE == 1;
   // ---- Eq. (1) for the words that a frame completed (events 0..nev-1 of buffer
   // H), by one wavefront for 4 to kWaveWords words at a time: lane 4 el + j holds
   // sub-beam j of word el.  No barrier: each of the nw wavefronts that score
   // takes its own words.
-  //   * the pairs (word, sub-beam) of equal group -- n-gram context and
-  //     completed-word node -- share the lookups of the first of them;
+  //   * a word's sub-beams of equal n-gram context share the lookups of the
+  //     first of them;
   //   * round 1: the lookups of the groups with few homophones, and one task
   //     per heavy group for the continuation index; round 2: the heavy groups'
   //     listed homophones (or all, if the list is long).  A task takes four
@@ -933,9 +936,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       uint32_t rr = 0, woff = 0, Hn = 0, ph = 0;
       int nsub = 0;
       double Lw = kNegInf;
-      Ctx ctx{};
+      HistNode par{};      // the pair's history node
+      uint4 top0{}, top1{}, top2{}, top3{};  // a heavy word's first homophones in unigram order (WordRank)
       int32_t w0 = 0, w1 = 0;
-      unsigned long long key = 0;
       if (word) {
         int k = e;
 #pragma unroll
@@ -946,30 +949,42 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         rr = sEvBeam[k];
         woff = sEvWoff[k];
         Hn = sEvH[k];
-        nsub = (H.meta[rr] >> 8) & 0xFF;
+        nsub = static_cast<int>(rr >> 16);
+        rr &= 0xFFFFu;
       }
       const bool pair = word && j < nsub;
+      const bool heavy = Hn >= Pr.heavy_min;
       if (pair) {
         ph = H.hist[rr * kMaxSub + j];
         Lw = H.Lw[rr * kMaxSub + j];
-        ctx = ctx_of(Sr.arena[ph]);
+        par = Sr.arena[ph];
         w0 = Sr.trie_words[woff];
         if (Hn > 1) w1 = Sr.trie_words[woff + 1];
-        key = group_key(ctx, woff);
       }
-      // the groups: every pair's first lane of equal key
+      // (in every lane of the word: the k-th winner's node is written by lane k,
+      // which may hold no sub-beam)
+      if (kAhead && word && heavy) {
+        const uint4* const wr = reinterpret_cast<const uint4*>(Sr.wrank + woff);
+        top0 = wr[0];
+        if (Hn > 1) top1 = wr[1];
+        if (Hn > 2) top2 = wr[2];
+        if (Hn > 3) top3 = wr[3];
+      }
+      const Ctx ctx = ctx_of(par);
+      // the groups: the first of the word's sub-beams with the same context
       int lead = lane;
-      for (uint64_t left = __ballot(pair); left;) {
-        const int l = __builtin_ctzll(left);
-        const uint64_t kl =
-            static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key), l)) |
-            (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key >> 32), l))) << 32);
-        const bool same = pair && key == kl;
-        if (same) lead = l;
-        left &= ~__ballot(same);
+      {
+        const uint64_t key = pair ? group_key(ctx, woff) : ~static_cast<uint64_t>(lane);
+        const uint32_t klo = static_cast<uint32_t>(key), khi = static_cast<uint32_t>(key >> 32);
+        const int q0 = lane & ~(kMaxSub - 1);
+        // (every lane takes part in each move: a source lane that is masked off gives 0)
+        const uint32_t l2 = quad_bcast<2>(klo), h2 = quad_bcast<2>(khi), l1 = quad_bcast<1>(klo), h1 = quad_bcast<1>(khi),
+                       l0 = quad_bcast<0>(klo), h0 = quad_bcast<0>(khi);
+        if (l2 == klo && h2 == khi && j > 2) lead = q0 + 2;
+        if (l1 == klo && h1 == khi && j > 1) lead = q0 + 1;
+        if (l0 == klo && h0 == khi && j > 0) lead = q0;
       }
       const bool leader = pair && lead == lane;
-      const bool heavy = Hn >= Pr.heavy_min;
       const uint64_t below = (1ull << lane) - 1ull;
       // round 1's tasks and results (a heavy group's task has no result of its own)
       int cnt = leader ? (heavy ? 1 : static_cast<int>(Hn)) : 0;
@@ -1158,6 +1173,16 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
                           (static_cast<double>(c.bo2) + (static_cast<double>(c.bo1) + static_cast<double>(logp)));
         return lw + Pr.comega * lp;
       };
+      // the word's k-th homophone in unigram order
+      auto ranked = [&](uint32_t k) -> WordRank {
+        auto pick = [&](uint32_t a, uint32_t b, uint32_t c, uint32_t d) -> uint32_t {
+          return k < 2 ? (k == 0 ? a : b) : (k == 2 ? c : d);
+        };
+        uint4 v = {pick(top0.x, top1.x, top2.x, top3.x), pick(top0.y, top1.y, top2.y, top3.y),
+                   pick(top0.z, top1.z, top2.z, top3.z), pick(top0.w, top1.w, top2.w, top3.w)};
+        if (!kAhead || k >= kTopWords) v = reinterpret_cast<const uint4*>(Sr.wrank + woff)[k];
+        return __builtin_bit_cast(WordRank, v);
+      };
       if (!many && pair) {
         const int nl = static_cast<int>(gc & ~kGroupHeavy);
         for (int m = 0; m < nl; ++m)
@@ -1168,8 +1193,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           // above the next word's
           int got = 0;
           double Lth = HUGE_VAL;
+#pragma unroll 1
           for (uint32_t k = 0; k < Hn; ++k) {
-            const WordRank wr = Sr.wrank[woff + k];
+            const WordRank wr = ranked(k);
             const double L = unigram_score(ctx, Lw, wr.logp);
             if (got >= O && Lth > L) break;
             bool member = false;
@@ -1325,14 +1351,26 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       }
       // history nodes (o reserved per word, in order), one lane per kept sub-beam
       const bool room = static_cast<uint64_t>(arena_n) + static_cast<uint64_t>(e + 1) * O <= Sr.arena_cap;
-      const uint32_t pn =
-          static_cast<uint32_t>(__shfl(static_cast<int>(ph), (lane & ~(kMaxSub - 1)) + ((myq >> 16) & (kMaxSub - 1)), 64));
+      // (the parent: the history node of the winner's sub-beam, in that lane)
+      const int pl = (lane & ~(kMaxSub - 1)) + ((myq >> 16) & (kMaxSub - 1));
+      const uint32_t pn = static_cast<uint32_t>(__shfl(static_cast<int>(ph), pl, 64));
+      HistNode pr;
+      if constexpr (kAhead) {
+        pr.blk = static_cast<uint32_t>(__shfl(static_cast<int>(par.blk), pl, 64));
+        pr.depth = static_cast<uint32_t>(__shfl(static_cast<int>(par.depth), pl, 64));
+        pr.word = __shfl(par.word, pl, 64);
+        pr.sfus = __shfl(par.sfus, pl, 64);
+#pragma unroll
+        for (int i = 0; i < kHistBlock - 2; ++i) pr.w[i] = __shfl(par.w[i], pl, 64);
+      } else if (word && room && j < kept) {
+        pr = Sr.arena[pn];
+      }
       if (word && room && j < kept) {
         QState st;
         if (mys >= 0) {
           st = mys < kLmRes ? W.st[mys] : scrS[gbase + mys];
         } else {
-          const WordRank wr = Sr.wrank[woff + static_cast<uint32_t>(-1 - mys)];
+          const WordRank wr = ranked(static_cast<uint32_t>(-1 - mys));
           st.c2 = kNone;
           st.c3 = kNone;
           st.bo2 = 0.0f;
@@ -1340,7 +1378,6 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           st.w = wr.w;
           st.bo1 = wr.bo;
         }
-        const HistNode par = Sr.arena[pn];
         HistNode hn;
         hn.word = st.w;
         hn.c2 = st.c2;
@@ -1348,14 +1385,14 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         hn.bo1 = st.bo1;
         hn.bo2 = st.bo2;
         hn.bo3 = st.bo3;
-        hn.depth = par.depth + 1;
-        hn.sfus = synth ? par.sfus + bigram_score(Pr, par.word, st.w) : 0.0;
+        hn.depth = pr.depth + 1;
+        hn.sfus = synth ? pr.sfus + bigram_score(Pr, pr.word, st.w) : 0.0;
         // a parent that ends a block (the root included) starts a new one
-        const bool starts = par.depth % kHistBlock == 0;
-        hn.blk = starts ? pn : par.blk;
-        hn.w[0] = starts ? -1 : par.word;
+        const bool starts = pr.depth % kHistBlock == 0;
+        hn.blk = starts ? pn : pr.blk;
+        hn.w[0] = starts ? -1 : pr.word;
 #pragma unroll
-        for (int i = 1; i < kHistBlock - 1; ++i) hn.w[i] = starts ? -1 : par.w[i - 1];
+        for (int i = 1; i < kHistBlock - 1; ++i) hn.w[i] = starts ? -1 : pr.w[i - 1];
         const uint32_t node = arena0 + arena_n + static_cast<uint32_t>(e * O + j);
         Sr.arena[node] = hn;
         H.Lw[rr * kMaxSub + j] = myL;
@@ -1392,6 +1429,11 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     BeamLds<KMAX>& N = sBeam[DB ? (cur ^ 1) : 0];  // the new ones (the same buffer when !DB)
     const double* const Dc = sD[row];              // the frame's scaled log-probs
     const bool more = tau + 1 < tend;
+    bool fuses = false;
+    if (fuse_frames) {
+      const int64_t t = t0 + tau;
+      fuses = t > 0 && t % P.fusion_interval == 0;
+    }
 
     // the next frame's log-probs are loaded meanwhile
     if (wave == NW - 1 && lane < kClasses && more)
@@ -1933,12 +1975,13 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       const uint64_t evs = __ballot(is_event);
       if (is_event) {
         const int k = 64 * wave + __popcll(evs & ((1ull << lane) - 1ull));
-        sEvBeam[k] = static_cast<uint32_t>(r);
+        sEvBeam[k] = static_cast<uint32_t>(r) | (((w_meta >> 8) & 0xFFu) << 16);  // hypothesis, its sub-beams
         sEvWoff[k] = ev_woff;
         sEvH[k] = ev_H;
       }
       if (lane == 0) sEvCnt[wave] = __popcll(evs);
     }
+    if (!kSplit || wave >= RW) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (the frame before's history nodes)
     lds_barrier();  // the new hypotheses, their keys and the completed words are in place
     mark(kPhNewBeam);
     int nev = 0;
@@ -1951,7 +1994,10 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     // to spare scores first.)
     if (!kSplit || (wave >= RW && wave < RW + LMW)) {
       score_words(P, S, N, nev, kSplit ? wave - RW : wave, LMW, lane);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // history nodes: read by the fusion and the next frames
+      // the history nodes (global memory) are read by the fusion, if this frame
+      // fuses, else by the next frame's scoring: then they are waited for at
+      // the end of its selection
+      if (fuses || !more) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     }
     if (wave < RW) {
       if (more) recombine(P, N, sD[row ^ 1], nsel, tid);
@@ -1976,8 +2022,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     // ---- Eq. (2) on fusion frames: the top-F hypotheses by (total desc, key
     // asc); each sub-beam's score becomes phi * its synthetic fusion score and
     // the sub-beams are re-ranked (stable)
-    const int64_t t = t0 + tau;
-    if (fuse_frames && t > 0 && t % P.fusion_interval == 0) {
+    if (fuses) {
       double* sc = reinterpret_cast<double*>(sSel);
       uint64_t* ky = reinterpret_cast<uint64_t*>(sSel + 8 * KMAX);
       uint32_t* ix = reinterpret_cast<uint32_t*>(sSel + 16 * KMAX);
