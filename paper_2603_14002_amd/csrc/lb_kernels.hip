@@ -616,7 +616,8 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // ~2.5 probes, and the whole frame 6 % longer)
   constexpr int HS = HSF * KMAX;
   static_assert(HSF >= 4 && (HSF & (HSF - 1)) == 0, "hash slots: a power of two, load at most 1/4");
-  static_assert(KMAX <= 256, "a hash slot holds its hypothesis in 8 bits");
+  constexpr int kIdxBits = 9;  // (never all ones: no slot equals kEmptyKey)
+  static_assert(KMAX < (1 << kIdxBits) - 1, "a hash slot holds its hypothesis in kIdxBits bits");
   constexpr int NW = BLOCK / 64;
   constexpr int NC = (kSep + LPB - 1) / LPB;  // extension slots per lane
   static_assert(LPB * NC >= kSep && NC + 2 <= 32, "a lane's candidates (its slots, the stay and the repeat) fit a 32-bit set");
@@ -638,12 +639,10 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   constexpr int kBinShift = 16 - kBinBits;  // of a 16-bit score
   constexpr int SEL_BYTES = kBoundaryCap * 20;
   constexpr int LM_BYTES = LMW * static_cast<int>(sizeof(LmWave));
-  // in place: the new hypotheses' sub-beams on their way; K >= 128: the top F
-  constexpr int STAGE_BYTES = DB ? 0 : 12 * KMAX * kMaxSub;
+  // K >= 128: the top F
   constexpr int FUSE_BYTES = KMAX >= 128 ? 4 * kBins + 24 * KMAX : 20 * KMAX;
   constexpr int MAX1 = SEL_BYTES > LM_BYTES ? SEL_BYTES : LM_BYTES;
-  constexpr int MAX2 = STAGE_BYTES > FUSE_BYTES ? STAGE_BYTES : FUSE_BYTES;
-  constexpr int UNI_BYTES = MAX1 > MAX2 ? MAX1 : MAX2;
+  constexpr int UNI_BYTES = MAX1 > FUSE_BYTES ? MAX1 : FUSE_BYTES;
   static_assert(20 * KMAX <= SEL_BYTES, "output sort scratch");
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
@@ -652,7 +651,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   const int len = lengths[b];
   const int tend = len < tau1 ? len : tau1;
 
-  __shared__ BeamLds<KMAX> sBeam[DB ? 2 : 1];
+  __shared__ __align__(16) BeamLds<KMAX> sBeam[DB ? 2 : 1];
   // this frame's row and the next one's: classes 0..40; 41..63 are zero (slots past the separator)
   __shared__ double sD[2][64];
   // the row for the 16-bit scores: Dtop, the largest of D + bonus over symbols
@@ -669,8 +668,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // are written (in the previous frame, or when the beam is loaded), cleared
   // once this frame's parent lookups are done (the frame's later barriers
   // separate the clear from the next inserts)
+  // (a slot: the key's bits from kIdxBits on, and the hypothesis below them, so
+  // that one read finds both; a full match is checked against the hypothesis)
   __shared__ unsigned long long sHKey[HS];
-  __shared__ uint8_t sHIdx[HS];  // the slot's hypothesis (KMAX <= 256)
   // top-K selection scratch; the LM step, the fusion and the output reuse it
   __shared__ __align__(16) unsigned char sSel[UNI_BYTES];
   __shared__ __align__(16) uint32_t sHisto[kBins];  // zero at the start of a frame
@@ -678,7 +678,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   __shared__ int32_t sLvBeta[kMaxLevels], sLvShift[kMaxLevels];
   __shared__ uint32_t sSelSrc[KMAX];
   // hypotheses that completed a word this frame: those of wavefront w from 64 w on
-  __shared__ uint32_t sEvBeam[KMAX], sEvWoff[KMAX], sEvH[KMAX];
+  __shared__ uint4 sEv[KMAX];
   __shared__ int32_t sEvCnt[RW];
   __shared__ double sRed[2 * NW], sRedB[2 * NW];
   __shared__ int32_t sScan[NW], sScanB[NW], sScanD[NW];
@@ -709,9 +709,6 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   double* const sBScore = reinterpret_cast<double*>(sSel);
   uint64_t* const sBKey = reinterpret_cast<uint64_t*>(sSel + kBoundaryCap * 8);
   uint32_t* const sBSrc = reinterpret_cast<uint32_t*>(sSel + kBoundaryCap * 16);
-  // write-back staging of the sub-beams (one-buffer instances)
-  double* const sStL = reinterpret_cast<double*>(sSel);
-  uint32_t* const sStH = reinterpret_cast<uint32_t*>(sStL + KMAX * kMaxSub);
   LmWave* const sLm = reinterpret_cast<LmWave*>(sSel);
   // the output (when this launch writes it) sorts in the shared scratch
   auto output = [&](const DevParams& Pr, const DevState& Sr) {
@@ -727,6 +724,20 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   const size_t gb = static_cast<size_t>(b) * P.K;
   const int O = P.O;
   const bool synth = P.fusion_source == 1;
+  // parameters that every frame waits for, in scalar registers (spilled ones cost
+  // a lane read, a load from the constant cache a hundred cycles and more)
+  const int K = P.K;
+  const double theta = P.theta;
+  const bool merge_max = P.merge_max != 0;
+  const TrieNode* const trie = S.trie;
+  HistNode* const arena = S.arena;
+  const WordRank* const wrank = S.wrank;
+  const int32_t* const trie_words = S.trie_words;
+  const Unigram* const uni = S.uni;
+  const uint32_t heavy_min = P.heavy_min;
+  const double comega = P.comega, lam = P.lam;
+  const uint64_t arena_cap = S.arena_cap;
+  const uint32_t word_scratch = static_cast<uint32_t>(S.scap) / static_cast<uint32_t>(P.K);  // lookup results of a word
   const bool fuse_frames = synth && P.fusion_interval > 0;
   const int64_t t0 = S.t0[b];
   const uint32_t arena0 = 1u + static_cast<uint32_t>(static_cast<uint64_t>(b) * S.arena_cap);
@@ -780,14 +791,8 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // a new hypothesis' prefix key into the hash table, with its index r
   auto insert_key = [&](uint64_t key, int r) {
     uint32_t s = static_cast<uint32_t>(key) & (HS - 1);
-    for (;;) {
-      const unsigned long long prev = atomicCAS(&sHKey[s], kEmptyKey, key);
-      if (prev == kEmptyKey) {
-        sHIdx[s] = static_cast<uint8_t>(r);
-        break;
-      }
-      s = (s + 1) & (HS - 1);
-    }
+    const unsigned long long entry = ((key >> kIdxBits) << kIdxBits) | static_cast<unsigned long long>(r);
+    while (atomicCAS(&sHKey[s], kEmptyKey, entry) != kEmptyKey) s = (s + 1) & (HS - 1);
   };
   uint32_t lines = 0, plines = 0, c_words = 0, c_look = 0;  // per thread
   uint64_t c_queries = 0;
@@ -860,37 +865,38 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // Reads nothing that Eq. (1) writes (it adds the word-level scores later), so
   // the wavefronts that hold the hypotheses run it while the others score the
   // words that the frame before completed.
-  auto recombine = [&](const DevParams& Pr, BeamLds<KMAX>& H, const double* D, int nh, int tid) {
-    if (tid < nh) {
-      const uint64_t pkey = H.pkey[tid];
-      const int last = H.meta[tid] & 0xFF;
-      int par = -1;
+  auto recombine = [&](BeamLds<KMAX>& H, const double* D, int tid, uint64_t pkey, uint32_t meta, double pt, double anb) {
+    {
+      const int last = meta & 0xFF;
+      const double ab2 = pt + D[0];
+      const double dl = D[last], bl = sBonus[last];
+      const double rep = last ? anb + dl : kNegInf;
+      double ext = kNegInf;
       if (pkey != kNoParent) {
         uint32_t s = static_cast<uint32_t>(pkey) & (HS - 1);
         for (int probes = 0; probes < HS; ++probes) {
-          const unsigned long long k = sHKey[s];
-          if (k == kEmptyKey) break;
-          if (k == pkey) {
-            par = static_cast<int>(sHIdx[s]);
-            break;
+          const unsigned long long e = sHKey[s];
+          if (e == kEmptyKey) break;
+          if (((e ^ pkey) >> kIdxBits) == 0) {
+            const int par = static_cast<int>(e & ((1u << kIdxBits) - 1u));
+            const uint64_t pk = H.key[par];
+            const int plast = H.meta[par] & 0xFF;
+            const double pab = H.ab[par], ppt = H.pt[par];
+            if (pk == pkey) {
+              atomicOr(reinterpret_cast<unsigned long long*>(&sCut[par]), 1ull << last);
+              ext = ((last == plast ? pab : ppt) + dl) + bl;
+              break;
+            }
           }
           s = (s + 1) & (HS - 1);
         }
-        if (par >= 0) atomicOr(reinterpret_cast<unsigned long long*>(&sCut[par]), 1ull << last);
-      }
-      const double ab2 = H.pt[tid] + D[0];
-      const double rep = last ? H.anb[tid] + D[last] : kNegInf;
-      double ext = kNegInf;
-      if (par >= 0) {
-        const double base = (last == static_cast<int>(H.meta[par] & 0xFF)) ? H.ab[par] : H.pt[par];
-        ext = (base + D[last]) + sBonus[last];
       }
       // anb2 = merge(rep, ext), then pt2 = merge(ab2, anb2); merge is
       // log-sum-exp, or max for the best-alignment recombination
       double x = rep, y = ext, anb2 = 0.0;
 #pragma unroll 1
       for (int pass = 0; pass < 2; ++pass) {
-        const double l = Pr.merge_max ? fmax(x, y) : lse2(x, y, [&](int k) { return sAtanh[k]; });
+        const double l = merge_max ? fmax(x, y) : lse2(x, y, [&](int k) { return sAtanh[k]; });
         if (pass == 0) {
           anb2 = l;
           x = ab2;
@@ -946,25 +952,25 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           if (left >= 0 && left < sEvCnt[w]) k = 64 * w + left;
           left -= sEvCnt[w];
         }
-        rr = sEvBeam[k];
-        woff = sEvWoff[k];
-        Hn = sEvH[k];
-        nsub = static_cast<int>(rr >> 16);
-        rr &= 0xFFFFu;
+        const uint4 ev = sEv[k];
+        rr = ev.x;
+        nsub = static_cast<int>(ev.y);
+        woff = ev.z;
+        Hn = ev.w;
       }
       const bool pair = word && j < nsub;
-      const bool heavy = Hn >= Pr.heavy_min;
+      const bool heavy = Hn >= heavy_min;
       if (pair) {
         ph = H.hist[rr * kMaxSub + j];
         Lw = H.Lw[rr * kMaxSub + j];
-        par = Sr.arena[ph];
-        w0 = Sr.trie_words[woff];
-        if (Hn > 1) w1 = Sr.trie_words[woff + 1];
+        par = arena[ph];
+        w0 = trie_words[woff];
+        if (Hn > 1) w1 = trie_words[woff + 1];
       }
       // (in every lane of the word: the k-th winner's node is written by lane k,
       // which may hold no sub-beam)
       if (kAhead && word && heavy) {
-        const uint4* const wr = reinterpret_cast<const uint4*>(Sr.wrank + woff);
+        const uint4* const wr = reinterpret_cast<const uint4*>(wrank + woff);
         top0 = wr[0];
         if (Hn > 1) top1 = wr[1];
         if (Hn > 2) top2 = wr[2];
@@ -998,7 +1004,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       uint64_t gmask = 0;  // (leaders) heavy: bit h mod 64 of every listed homophone h
       // a batch's results past those that LDS holds: the stream's scratch, from
       // the words before it on
-      const size_t gbase = static_cast<size_t>(e0) * (static_cast<uint32_t>(Sr.scap) / static_cast<uint32_t>(Pr.K));
+      const size_t gbase = static_cast<size_t>(e0) * word_scratch;
       mark(kPhGroup);
 #pragma unroll 1
       for (int round = 0; round < 2; ++round) {
@@ -1021,15 +1027,15 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           const uint32_t gc = static_cast<uint32_t>(__shfl(static_cast<int>(gcnt), own, 64));
           const int a0 = __shfl(w0, own, 64), a1 = __shfl(w1, own, 64);
           uint32_t* const E = scrE + static_cast<size_t>(e0 * kMaxSub + own) * kMaxExplicit;
-          const bool index = round == 0 && gH >= Pr.heavy_min;
+          const bool index = round == 0 && gH >= heavy_min;
           uint32_t id = gw;
           if (task && !index) {
             uint32_t h = k;
             if (round == 1 && (gc & kGroupHeavy)) h = E[k];
-            id = static_cast<uint32_t>(h == 0 ? a0 : (h == 1 ? a1 : Sr.trie_words[gw + h]));
+            id = static_cast<uint32_t>(h == 0 ? a0 : (h == 1 ? a1 : trie_words[gw + h]));
           }
           Unigram un{0.0f, 0.0f};
-          if (task && !index && o == 3) un = Sr.uni[id];
+          if (task && !index && o == 3) un = uni[id];
           Hit hit{kNone, 0, 0};
           const uint32_t cid = o == 0 ? x1 : (o == 1 ? x2 : x3);
           if (task && o < 3 && (o == 0 || cid != kNone)) {
@@ -1171,7 +1177,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       auto unigram_score = [&](const Ctx& c, double lw, float logp) -> double {
         const double lp = static_cast<double>(c.bo3) +
                           (static_cast<double>(c.bo2) + (static_cast<double>(c.bo1) + static_cast<double>(logp)));
-        return lw + Pr.comega * lp;
+        return lw + comega * lp;
       };
       // the word's k-th homophone in unigram order
       auto ranked = [&](uint32_t k) -> WordRank {
@@ -1180,13 +1186,13 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         };
         uint4 v = {pick(top0.x, top1.x, top2.x, top3.x), pick(top0.y, top1.y, top2.y, top3.y),
                    pick(top0.z, top1.z, top2.z, top3.z), pick(top0.w, top1.w, top2.w, top3.w)};
-        if (!kAhead || k >= kTopWords) v = reinterpret_cast<const uint4*>(Sr.wrank + woff)[k];
+        if (!kAhead || k >= kTopWords) v = reinterpret_cast<const uint4*>(wrank + woff)[k];
         return __builtin_bit_cast(WordRank, v);
       };
       if (!many && pair) {
         const int nl = static_cast<int>(gc & ~kGroupHeavy);
         for (int m = 0; m < nl; ++m)
-          insert(Lw + Pr.comega * res_lp(off + m), (j << 16) | static_cast<int>(walk ? E[m] : static_cast<uint32_t>(m)), off + m);
+          insert(Lw + comega * res_lp(off + m), (j << 16) | static_cast<int>(walk ? E[m] : static_cast<uint32_t>(m)), off + m);
         if (walk) {
           // the heavy group's other homophones in unigram order (scores
           // non-increasing), until its o-th such candidate scores strictly
@@ -1222,7 +1228,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           argmax_step<kDppXor1>(&bL, &bq, &bs);
           argmax_step<kDppXor2>(&bL, &bq, &bs);
           if (k == 0) bestL = bL;
-          open = open && bL != kNegInf && !(bL < bestL - Pr.lam);
+          open = open && bL != kNegInf && !(bL < bestL - lam);
           if (open) {
             if (j == k) {
               myL = bL;
@@ -1280,7 +1286,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           const uint32_t xc = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(gc), l0 + jj));
           const int xo = __builtin_amdgcn_readlane(off, l0 + jj);
           if (!(xc & kGroupHeavy)) {
-            for (int h = lane; h < xH; h += 64) put(lw + Pr.comega * res_lp(xo + h), (jj << 16) | h, xo + h);
+            for (int h = lane; h < xH; h += 64) put(lw + comega * res_lp(xo + h), (jj << 16) | h, xo + h);
           } else {
             // lane m holds the m-th listed homophone, a candidate with its
             // looked-up score; the others in unigram order, 64 at a time, until
@@ -1290,7 +1296,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
             uint32_t eh = kNone;
             if (lane < ne) {
               eh = scrE[static_cast<size_t>(e0 * kMaxSub + xl) * kMaxExplicit + lane];
-              put(lw + Pr.comega * res_lp(xo + lane), (jj << 16) | static_cast<int>(eh), xo + lane);
+              put(lw + comega * res_lp(xo + lane), (jj << 16) | static_cast<int>(eh), xo + lane);
             }
             Ctx cx{};
             cx.bo1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ctx.bo1), l0 + jj));
@@ -1302,7 +1308,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
               const int k = c0 + lane;
               const bool valid = k < xH;
               WordRank wr = WordRank{0, 0.0f, 0.0f, kNone};
-              if (valid) wr = Sr.wrank[xw + k];
+              if (valid) wr = wrank[xw + k];
               const int last = (xH - 1 - c0) < 63 ? xH - 1 - c0 : 63;
               bool member = false;
               for (int m = 0; m < ne; ++m)
@@ -1326,7 +1332,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           wave_argmax(&bL, &bq);
           if (bL == kNegInf) break;
           if (k == 0) xbest = bL;
-          if (bL < xbest - Pr.lam) break;
+          if (bL < xbest - lam) break;
           const bool holder = sL[0] == bL && sq[0] == bq;  // one lane: queries are distinct
           const int hl = __builtin_ctzll(__ballot(holder));
           const int bs = __builtin_amdgcn_readlane(ss[0], hl);
@@ -1350,7 +1356,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         if ((lane & ~(kMaxSub - 1)) == l0) kept = xkept;
       }
       // history nodes (o reserved per word, in order), one lane per kept sub-beam
-      const bool room = static_cast<uint64_t>(arena_n) + static_cast<uint64_t>(e + 1) * O <= Sr.arena_cap;
+      const bool room = static_cast<uint64_t>(arena_n) + static_cast<uint64_t>(e + 1) * O <= arena_cap;
       // (the parent: the history node of the winner's sub-beam, in that lane)
       const int pl = (lane & ~(kMaxSub - 1)) + ((myq >> 16) & (kMaxSub - 1));
       const uint32_t pn = static_cast<uint32_t>(__shfl(static_cast<int>(ph), pl, 64));
@@ -1363,7 +1369,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
 #pragma unroll
         for (int i = 0; i < kHistBlock - 2; ++i) pr.w[i] = __shfl(par.w[i], pl, 64);
       } else if (word && room && j < kept) {
-        pr = Sr.arena[pn];
+        pr = arena[pn];
       }
       if (word && room && j < kept) {
         QState st;
@@ -1394,7 +1400,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
 #pragma unroll
         for (int i = 1; i < kHistBlock - 1; ++i) hn.w[i] = starts ? -1 : pr.w[i - 1];
         const uint32_t node = arena0 + arena_n + static_cast<uint32_t>(e * O + j);
-        Sr.arena[node] = hn;
+        arena[node] = hn;
         H.Lw[rr * kMaxSub + j] = myL;
         H.hist[rr * kMaxSub + j] = node;
       }
@@ -1412,9 +1418,18 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   };
 
   // the first frame's hypotheses
-  if (wave < RW) recombine(P, sBeam[0], sD[0], n, tid);
+  if (tid < n) recombine(sBeam[0], sD[0], tid, sBeam[0].pkey[tid], sBeam[0].meta[tid], sBeam[0].pt[tid], sBeam[0].anb[tid]);
   lds_barrier();
   mark(kPhRecomb);
+  // frames until the next fusion frame (t > 0, a multiple of the interval); counted
+  // down, as a 64-bit remainder in every frame took hundreds of cycles
+  const int fuse_every = fuse_frames ? P.fusion_interval : 0x7FFFFFFF;
+  int fuse_in = 0x7FFFFFFF;
+  if (fuse_frames) {
+    const int64_t t = t0 + tau0;
+    const int past = static_cast<int>(t % fuse_every);
+    fuse_in = t > 0 && past == 0 ? 0 : fuse_every - past;
+  }
 
   for (int tau = tau0; tau < tend; ++tau) {
     // the thread index is made opaque to the optimizer in every frame so that
@@ -1429,11 +1444,8 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     BeamLds<KMAX>& N = sBeam[DB ? (cur ^ 1) : 0];  // the new ones (the same buffer when !DB)
     const double* const Dc = sD[row];              // the frame's scaled log-probs
     const bool more = tau + 1 < tend;
-    bool fuses = false;
-    if (fuse_frames) {
-      const int64_t t = t0 + tau;
-      fuses = t > 0 && t % P.fusion_interval == 0;
-    }
+    const bool fuses = fuse_in == 0;
+    fuse_in = fuses ? fuse_every - 1 : fuse_in - 1;
 
     // the next frame's log-probs are loaded meanwhile
     if (wave == NW - 1 && lane < kClasses && more)
@@ -1531,7 +1543,6 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       lds_barrier();
       return sNBinned;
     };
-    const double theta = P.theta;
     int nsel = 0;
     bool done = false;
 
@@ -1593,12 +1604,12 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       }
       lds_barrier();
       if (wave == NW - 1 && more) set_row(P, row ^ 1, dnext);
-      const int binned = find_bin(P.K);
+      const int binned = find_bin(K);
       const int bk = sBucket;
       // no candidate scores above top, the K-th at least low
       const double top = ref - static_cast<double>(sTopBin << kBinShift) * qunit;
       const double low = ref - static_cast<double>(((bk + 1) << kBinShift) + 4) * qunit;
-      done = binned >= P.K && bk < kBins - 1 && sWild != tau + 1 && low >= top - theta;
+      done = binned >= K && bk < kBins - 1 && sWild != tau + 1 && low >= top - theta;
       if (done) {
         const int ta = (bk << kBinShift) - 3;         // selected: below ta
         const int tb = ((bk + 1) << kBinShift) + 3;   // not selected: tb and above
@@ -1642,7 +1653,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           nsure += c;
         }
         const int nbc = sBCount;
-        const int need = P.K - nsure;
+        const int need = K - nsure;
         done = nbc <= kBoundaryCap && need >= 0 && need <= nbc;
         if (done) {
 #pragma unroll 1
@@ -1666,7 +1677,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
             rank += dpp_i32<kDppHalfMirror>(rank, 0);
             if ((tid & 7) == 0 && rank < need) sSelSrc[nsure + rank] = sBSrc[m];
           }
-          nsel = P.K;
+          nsel = K;
           btotal = top;
         }
       }
@@ -1756,14 +1767,14 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       if (bn != 0xFFFFu) atomicAdd(&sHisto[bn], 1u);
     }
     lds_barrier();
-    const int nbinned = find_bin(P.K);
+    const int nbinned = find_bin(K);
     // the K-th candidate's bin is resolved, or every binned candidate is selected
     int beta0 = kBins, nlev = 1, need = 0, nbc = 0, cntb = 0;
     bool all_bin = false;
-    const bool resolve = nbinned >= P.K;
+    const bool resolve = nbinned >= K;
     if (resolve) {
       beta0 = sBucket;
-      need = P.K - sAbove;
+      need = K - sAbove;
       cntb = sBucketCnt;
     }
     // level 0 decides every candidate outside the boundary bin: above it taken,
@@ -1864,8 +1875,8 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       if (take) sel_bits |= 1u << k;
     }
     int wpos = block_scan<BLOCK, false>(__popc(sel_bits), sScanD, &nsel);
-    if (nsel > P.K) {  // cannot happen when the selection is exact; never write past K entries
-      nsel = P.K;
+    if (nsel > K) {  // cannot happen when the selection is exact; never write past K entries
+      nsel = K;
       if (tid == 0) atomicOr(S.flags, kFlagSelect);
     }
 #pragma unroll 1
@@ -1874,7 +1885,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       sSelSrc[wpos++] = static_cast<uint32_t>(hi_) | (v << 16);
     }
     btotal = best;
-    coarse = nsel == P.K;
+    coarse = nsel == K;
     }
     lds_barrier();
     mark(kPhTopK);
@@ -1884,71 +1895,48 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     // are cleared meanwhile.)
     for (int d = tid; d < kBins; d += BLOCK) sHisto[d] = 0;
     if (tid == 0) sBCount = 0;
+    // Every field of an entry comes from its source in one round of reads, for
+    // a stay and an extension alike.
     const int r = tid;
-    int is_event = 0;
-    uint32_t ev_woff = 0, ev_H = 0;
+    const bool mine = r < nsel;
     bool tn_load = false;
     TrieNode tn{};
-    // every new entry's fields from its source, into registers first
     uint64_t w_key = 0, w_pkey = 0, w_tmask = 0;
     double w_ab = 0.0, w_anb = 0.0, w_pt = 0.0;
     uint32_t w_node = 0, w_meta = 0, w_first = 0, w_woff = 0;
-    if (r < nsel) {
+    uint4 w_L01{}, w_L23{}, w_hist{};  // the sub-beams: four word-level scores, four history nodes
+    bool is_event = false;
+    if (mine) {
       const uint32_t src = sSelSrc[r];
       const int i = src & 0xFFFF;
       const int v = src >> 16;
       const uint32_t meta_i = C.meta[i];
-      if (v == 0) {
-        w_key = C.key[i];
-        w_pkey = C.pkey[i];
-        w_ab = sAb2[i];
-        w_anb = sAnb2[i];
-        w_pt = sPt2[i];
-        w_node = C.node[i];
-        w_meta = meta_i;
-        w_tmask = C.tmask[i];
-        w_first = C.first[i];
-        w_woff = C.woff[i];
-      } else {
-        const int last = meta_i & 0xFF;
-        const double base = (v == last) ? C.ab[i] : C.pt[i];
-        const double anb = (base + Dc[v]) + sBonus[v];
-        const uint64_t tm = C.tmask[i];
-        w_key = prefix_step(C.key[i], v);
-        w_pkey = C.key[i];
-        w_ab = kNegInf;
-        w_anb = anb;
-        w_pt = anb;  // log-sum-exp(-inf, anb)
-        uint32_t child = kRootNode;
-        if (v != kSep) child = C.first[i] + __popcll(tm & ((1ull << v) - 1ull));
-        w_node = child;
-        w_meta = static_cast<uint32_t>(v) | (meta_i & 0xFF00u);
-        tn = S.trie[child];
-        tn_load = true;
-        if (v == kSep) {
-          is_event = 1;
-          ev_woff = C.woff[i];
-          ev_H = static_cast<uint32_t>(tm >> kWordCountShift);
-        }
-      }
-      const int nsub = (meta_i >> 8) & 0xFF;
-      if constexpr (DB) {
-        // two buffers: the sub-beams are copied straight across
-        for (int j = 0; j < nsub; ++j) {
-          N.Lw[r * kMaxSub + j] = C.Lw[i * kMaxSub + j];
-          N.hist[r * kMaxSub + j] = C.hist[i * kMaxSub + j];
-        }
-      } else {
-        // in place: the sub-beams go through the free part of the shared
-        // scratch (registers would spill)
-        for (int j = 0; j < nsub; ++j) {
-          sStL[r * kMaxSub + j] = C.Lw[i * kMaxSub + j];
-          sStH[r * kMaxSub + j] = C.hist[i * kMaxSub + j];
-        }
-      }
+      const uint64_t key_i = C.key[i], pkey_i = C.pkey[i];
+      const double ab_i = C.ab[i], pt_i = C.pt[i], ab2 = sAb2[i], anb2 = sAnb2[i], pt2 = sPt2[i];
+      const double dv = Dc[v], bv = sBonus[v];
+      const uint32_t node_i = C.node[i];
+      w_tmask = C.tmask[i];
+      w_first = C.first[i];
+      w_woff = C.woff[i];
+      w_L01 = reinterpret_cast<const uint4*>(&C.Lw[i * kMaxSub])[0];
+      w_L23 = reinterpret_cast<const uint4*>(&C.Lw[i * kMaxSub])[1];
+      w_hist = reinterpret_cast<const uint4*>(&C.hist[i * kMaxSub])[0];
+      tn_load = v != 0;
+      is_event = v == kSep;
+      const double base = v == static_cast<int>(meta_i & 0xFF) ? ab_i : pt_i;
+      const double ext = (base + dv) + bv;
+      const uint32_t child = is_event ? kRootNode : w_first + __popcll(w_tmask & ((1ull << v) - 1ull));
+      if (tn_load) tn = trie[child];
+      w_key = tn_load ? prefix_step(key_i, v) : key_i;
+      w_pkey = tn_load ? key_i : pkey_i;
+      w_ab = tn_load ? kNegInf : ab2;
+      w_anb = tn_load ? ext : anb2;
+      w_pt = tn_load ? ext : pt2;  // log-sum-exp(-inf, ext)
+      w_node = tn_load ? child : node_i;
+      w_meta = tn_load ? (static_cast<uint32_t>(v) | (meta_i & 0xFF00u)) : meta_i;
     }
     if constexpr (!DB) lds_barrier();  // every source entry has been read
-    if (r < nsel) {
+    if (mine) {
       insert_key(w_key, r);  // for the next frame's parent lookups
       sCut[r] = 0;
       N.key[r] = w_key;
@@ -1963,22 +1951,15 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         N.first[r] = w_first;
         N.woff[r] = w_woff;
       }
-      if constexpr (!DB) {
-        const int nsub = (w_meta >> 8) & 0xFF;
-        for (int j = 0; j < nsub; ++j) {
-          N.Lw[r * kMaxSub + j] = sStL[r * kMaxSub + j];
-          N.hist[r * kMaxSub + j] = sStH[r * kMaxSub + j];
-        }
-      }
+      reinterpret_cast<uint4*>(&N.Lw[r * kMaxSub])[0] = w_L01;
+      reinterpret_cast<uint4*>(&N.Lw[r * kMaxSub])[1] = w_L23;
+      reinterpret_cast<uint4*>(&N.hist[r * kMaxSub])[0] = w_hist;
     }
     if (wave < RW) {
       const uint64_t evs = __ballot(is_event);
-      if (is_event) {
-        const int k = 64 * wave + __popcll(evs & ((1ull << lane) - 1ull));
-        sEvBeam[k] = static_cast<uint32_t>(r) | (((w_meta >> 8) & 0xFFu) << 16);  // hypothesis, its sub-beams
-        sEvWoff[k] = ev_woff;
-        sEvH[k] = ev_H;
-      }
+      if (is_event)  // the hypothesis, its sub-beams, the completed word's node
+        sEv[64 * wave + __popcll(evs & ((1ull << lane) - 1ull))] =
+            uint4{static_cast<uint32_t>(r), (w_meta >> 8) & 0xFFu, w_woff, static_cast<uint32_t>(w_tmask >> kWordCountShift)};
       if (lane == 0) sEvCnt[wave] = __popcll(evs);
     }
     if (!kSplit || wave >= RW) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (the frame before's history nodes)
@@ -2000,7 +1981,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       if (fuses || !more) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     }
     if (wave < RW) {
-      if (more) recombine(P, N, sD[row ^ 1], nsel, tid);
+      if (more && mine) recombine(N, sD[row ^ 1], tid, w_pkey, w_meta, w_pt, w_anb);
       if (tn_load) {
         N.tmask[r] = tn.mask;
         N.first[r] = tn.first_child;
@@ -2011,7 +1992,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       // nodes reserved this frame; past the capacity the count stays at cap + 1
       // (every later word event then sees no room and raises the flag)
       const uint64_t an = static_cast<uint64_t>(arena_n) + static_cast<uint64_t>(nev * O);
-      arena_n = static_cast<uint32_t>(an <= S.arena_cap ? an : S.arena_cap + 1);
+      arena_n = static_cast<uint32_t>(an <= arena_cap ? an : arena_cap + 1);
     }
     if (tid == 0) sCnt[4] += static_cast<unsigned long long>(n) * kClasses;
     n = nsel;
