@@ -122,18 +122,6 @@ __device__ __forceinline__ void argmax_step(double* L, int* q) {
   *q = take ? oq : *q;
 }
 
-// The same with a payload that travels with the winner.
-template <int CTRL>
-__device__ __forceinline__ void argmax_step(double* L, int* q, int* s) {
-  const double oL = dpp_f64<CTRL>(*L, -HUGE_VAL);
-  const int oq = dpp_i32<CTRL>(*q, 0x7FFFFFFF);
-  const int os = dpp_i32<CTRL>(*s, 0);
-  const bool take = oL > *L || (oL == *L && oq < *q);
-  *L = take ? oL : *L;
-  *q = take ? oq : *q;
-  *s = take ? os : *s;
-}
-
 // Wavefront arg-max of (L desc, q asc), in every lane.
 __device__ __forceinline__ void wave_argmax(double* L, int* q) {
   argmax_step<kDppXor1>(L, q);
@@ -626,15 +614,14 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   static_assert(NH + 1 <= 16, "the pairs' sets: 16 bits a half");
   // the wavefronts that hold the hypotheses (one thread each), and those that
   // score completed words meanwhile: the others, as many as a beam can fill
-  // (every wavefront, before its other work, where none is left)
   constexpr int RW = (KMAX + 63) / 64;
-  constexpr bool kSplit = NW > RW;
   constexpr int kWordWaves = (KMAX + kWaveWords - 1) / kWaveWords;
-  constexpr int LMW = !kSplit ? NW : (NW - RW < kWordWaves ? NW - RW : kWordWaves);
+  constexpr int LMW = NW - RW < kWordWaves ? NW - RW : kWordWaves;
+  static_assert(NW > RW, "a wavefront to score words");
   // score bins of the top-K selection: 1024 at K = 256; 512 for the smaller
   // beams' fewer candidates (c5: 25.69 against 25.83 ms with 1024; c4 9.91
   // against 9.80 with 512)
-  constexpr int kBinBits = KMAX >= 256 ? 10 : 9;
+  constexpr int kBinBits = KMAX >= 128 ? 9 : 8;
   constexpr int kBins = 1 << kBinBits;
   constexpr int kBinShift = 16 - kBinBits;  // of a 16-bit score
   constexpr int SEL_BYTES = kBoundaryCap * 20;
@@ -682,7 +669,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   __shared__ int32_t sEvCnt[RW];
   __shared__ double sRed[2 * NW], sRedB[2 * NW];
   __shared__ int32_t sScan[NW], sScanB[NW], sScanD[NW];
-  __shared__ int32_t sBucket, sAbove, sBucketCnt, sBCount, sAthr, sNBinned, sTopBin;
+  __shared__ int32_t sBucket, sAbove, sBCount, sAthr;
   __shared__ int32_t sWild;  // the last frame (tau + 1) whose scores the 16-bit ones do not describe
   // counters: probed lines, completed words, LM queries, index lines (summed over
   // the threads at the end), expansions, fused hypotheses, lookups (added by
@@ -699,7 +686,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // scores words (taken after the barrier that ends the phase, or, inside Eq.
   // (1), where that wavefront is done with it)
   auto mark = [&](int k) {
-    if (timing && threadIdx.x == (kSplit ? 64 * RW : 0)) {
+    if (timing && threadIdx.x == 64 * RW) {
       const unsigned long long now = __builtin_amdgcn_s_memtime();
       sPhase[k] += now - sPhase[kPhases];
       sPhase[kPhases] = now;
@@ -830,12 +817,16 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       reinterpret_cast<uint16_t*>(&sDq[q][0])[h] = u < 65535.0 ? static_cast<uint16_t>(u) : uint16_t{65535};  // (also of NaN)
     }
   };
-  // the first frame's row now; in each frame the last wavefront loads the next
-  // frame's row early and sets it while the first one searches the top-K's bins
+  // the first two frames' rows now; in each frame the last wavefront loads the
+  // row after the next one's early, and sets it where this frame's was, beside
+  // the word scoring
   int row = 0;
+  auto load_row = [&](int t, int lane) -> float {
+    return lane < kClasses && t < tend ? logits[(static_cast<size_t>(b) * Tc + t) * kClasses + lane] : 0.0f;
+  };
   lds_barrier();
-  if (wave == 0)
-    set_row(P, 0, lane < kClasses ? logits[(static_cast<size_t>(b) * Tc + tau0) * kClasses + lane] : 0.0f);
+  if (wave == 0) set_row(P, 0, load_row(tau0, lane));
+  if (wave == 1) set_row(P, 1, load_row(tau0 + 1, lane));
   float dnext = 0.0f;
   lds_barrier();
   // the loaded hypotheses' keys for the first frame, and their best total
@@ -912,7 +903,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   };
 
   // (where the registers allow: read ahead what the ranking may need)
-  constexpr bool kAhead = WPE == 1;
+  constexpr bool kAhead = WPE < 4;
   // ---- Eq. (1) for the words that a frame completed (events 0..nev-1 of buffer
   // H), by one wavefront for 4 to kWaveWords words at a time: lane 4 el + j holds
   // sub-beam j of word el.  No barrier: each of the nw wavefronts that score
@@ -1191,7 +1182,14 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       };
       if (!many && pair) {
         const int nl = static_cast<int>(gc & ~kGroupHeavy);
-        for (int m = 0; m < nl; ++m)
+        // (the first candidate of an empty list is put there)
+        if (nl > 0) {
+          tL[0] = Lw + comega * res_lp(off);
+          tq[0] = (j << 16) | static_cast<int>(walk ? E[0] : 0u);
+          ts[0] = off;
+        }
+#pragma unroll 1
+        for (int m = 1; m < nl; ++m)
           insert(Lw + comega * res_lp(off + m), (j << 16) | static_cast<int>(walk ? E[m] : static_cast<uint32_t>(m)), off + m);
         if (walk) {
           // the heavy group's other homophones in unigram order (scores
@@ -1199,8 +1197,18 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           // above the next word's
           int got = 0;
           double Lth = HUGE_VAL;
+          uint32_t k = 0;
+          if (nl == 0) {
+            const WordRank wr = ranked(0);
+            tL[0] = unigram_score(ctx, Lw, wr.logp);
+            tq[0] = (j << 16) | static_cast<int>(wr.h);
+            ts[0] = -1;
+            got = 1;
+            if (O == 1) Lth = tL[0];
+            k = 1;
+          }
 #pragma unroll 1
-          for (uint32_t k = 0; k < Hn; ++k) {
+          for (; k < Hn; ++k) {
             const WordRank wr = ranked(k);
             const double L = unigram_score(ctx, Lw, wr.logp);
             if (got >= O && Lth > L) break;
@@ -1223,21 +1231,27 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
 #pragma unroll
       for (int k = 0; k < kMaxSub; ++k) {
         if (k < O) {
-          double bL = tL[0];
-          int bq = tq[0], bs = ts[0];
-          argmax_step<kDppXor1>(&bL, &bq, &bs);
-          argmax_step<kDppXor2>(&bL, &bq, &bs);
-          if (k == 0) bestL = bL;
-          open = open && bL != kNegInf && !(bL < bestL - lam);
+          // the best head; of equal ones the first in (sub-beam, homophone) order
+          double m4 = fmax(tL[0], dpp_f64<kDppXor1>(tL[0], kNegInf));
+          m4 = fmax(m4, dpp_f64<kDppXor2>(m4, kNegInf));
+          int q4 = tL[0] == m4 ? tq[0] : 0x7FFFFFFF;
+          q4 = min(q4, dpp_i32<kDppXor1>(q4, 0x7FFFFFFF));
+          q4 = min(q4, dpp_i32<kDppXor2>(q4, 0x7FFFFFFF));
+          const bool win = tL[0] == m4 && tq[0] == q4;
+          int s4 = win ? ts[0] : 0;
+          s4 |= dpp_i32<kDppXor1>(s4, 0);
+          s4 |= dpp_i32<kDppXor2>(s4, 0);
+          if (k == 0) bestL = m4;
+          open = open && m4 != kNegInf && !(m4 < bestL - lam);
           if (open) {
             if (j == k) {
-              myL = bL;
-              myq = bq;
-              mys = bs;
+              myL = m4;
+              myq = q4;
+              mys = s4;
             }
             kept = k + 1;
           }
-          if (tL[0] == bL && tq[0] == bq) {  // the holder (queries are distinct)
+          if (win) {
 #pragma unroll
             for (int m = 0; m + 1 < kMaxSub; ++m) {
               tL[m] = tL[m + 1];
@@ -1447,9 +1461,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     const bool fuses = fuse_in == 0;
     fuse_in = fuses ? fuse_every - 1 : fuse_in - 1;
 
-    // the next frame's log-probs are loaded meanwhile
-    if (wave == NW - 1 && lane < kClasses && more)
-      dnext = logits[(static_cast<size_t>(b) * Tc + tau + 1) * kClasses + lane];
+    if (wave == NW - 1) dnext = load_row(tau + 2, lane);
     for (int s = tid; s < HS; s += BLOCK) sHKey[s] = kEmptyKey;  // for the new hypotheses' keys
     // Workgroups that share a CU: the CU's arbitration favours the older
     // wavefronts, so the workgroup dispatched second (the later half of the
@@ -1497,51 +1509,52 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       const uint64_t k = C.key[hi_];
       return v == 0 ? k : prefix_step(k, v);
     };
-    // finds the bin holding the need-th candidate of sHisto (sBucket, sAbove,
-    // sBucketCnt) and a bin that no candidate lies above (sTopBin); returns the
-    // number of binned candidates.  The first wavefront scans the bins, kBins /
-    // 64 per lane, so one barrier ends it.
-    auto find_bin = [&](int need_in) -> int {
+    // The bin that holds the need-th candidate of sHisto, the candidates above
+    // and in it (bin kBins: fewer than need candidates), and a bin that no
+    // candidate lies above.  Every wavefront scans the bins, kBins / 64 per
+    // lane, and has the result in scalar registers: one scan and a barrier for
+    // its result took twice as long.
+    struct Found {
+      int bin, above, count, top;
+    };
+    auto find_bin = [&](int need_in) -> Found {
       constexpr int PERW = kBins / 64;
       static_assert(PERW % 4 == 0, "bins per lane in 16-B loads");
-      if (wave == 0) {
-        int h[PERW];
-        const uint4* hp = reinterpret_cast<const uint4*>(sHisto + lane * PERW);
+      int h[PERW];
+      const uint4* hp = reinterpret_cast<const uint4*>(sHisto + lane * PERW);
 #pragma unroll
-        for (int q = 0; q < PERW / 4; ++q) {
-          const uint4 x4 = hp[q];
-          h[4 * q] = static_cast<int>(x4.x);
-          h[4 * q + 1] = static_cast<int>(x4.y);
-          h[4 * q + 2] = static_cast<int>(x4.z);
-          h[4 * q + 3] = static_cast<int>(x4.w);
-        }
-        int local = 0;
-#pragma unroll
-        for (int q = 0; q < PERW; ++q) local += h[q];
-        const int incl = wave_scan_incl(local);
-        const int before = incl - local;
-        const uint64_t some = __ballot(local > 0);
-        if (lane == 63) {
-          sNBinned = incl;
-          sTopBin = some ? __builtin_ctzll(some) * PERW : 0;
-        }
-        if (before < need_in && incl >= need_in) {
-          int acc = before;
-          bool found = false;
-#pragma unroll
-          for (int q = 0; q < PERW; ++q) {
-            if (!found && acc + h[q] >= need_in) {
-              sBucket = lane * PERW + q;
-              sAbove = acc;
-              sBucketCnt = h[q];
-              found = true;
-            }
-            acc += h[q];
-          }
-        }
+      for (int q = 0; q < PERW / 4; ++q) {
+        const uint4 x4 = hp[q];
+        h[4 * q] = static_cast<int>(x4.x);
+        h[4 * q + 1] = static_cast<int>(x4.y);
+        h[4 * q + 2] = static_cast<int>(x4.z);
+        h[4 * q + 3] = static_cast<int>(x4.w);
       }
-      lds_barrier();
-      return sNBinned;
+      int local = 0;
+#pragma unroll
+      for (int q = 0; q < PERW; ++q) local += h[q];
+      const int incl = wave_scan_incl(local);
+      const int before = incl - local;
+      const uint64_t some = __ballot(local > 0);
+      const uint64_t hit = __ballot(before < need_in && incl >= need_in);
+      // this lane's bin, were it the one: the first q whose sum reaches need_in
+      int bin = 0, above = before, count = h[0];
+#pragma unroll
+      for (int q = 1, acc = before; q < PERW; ++q) {
+        acc += h[q - 1];
+        const bool past = acc < need_in;
+        bin = past ? q : bin;
+        above = past ? acc : above;
+        count = past ? h[q] : count;
+      }
+      Found f{kBins, 0, 0, some ? static_cast<int>(__builtin_ctzll(some)) * PERW : 0};
+      if (hit) {
+        const int l = __builtin_ctzll(hit);
+        f.bin = l * PERW + __builtin_amdgcn_readlane(bin, l);
+        f.above = __builtin_amdgcn_readlane(above, l);
+        f.count = __builtin_amdgcn_readlane(count, l);
+      }
+      return f;
     };
     int nsel = 0;
     bool done = false;
@@ -1603,13 +1616,12 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         }
       }
       lds_barrier();
-      if (wave == NW - 1 && more) set_row(P, row ^ 1, dnext);
-      const int binned = find_bin(K);
-      const int bk = sBucket;
+      const Found f = find_bin(K);
+      const int bk = f.bin;
       // no candidate scores above top, the K-th at least low
-      const double top = ref - static_cast<double>(sTopBin << kBinShift) * qunit;
+      const double top = ref - static_cast<double>(f.top << kBinShift) * qunit;
       const double low = ref - static_cast<double>(((bk + 1) << kBinShift) + 4) * qunit;
-      done = binned >= K && bk < kBins - 1 && sWild != tau + 1 && low >= top - theta;
+      done = bk < kBins - 1 && sWild != tau + 1 && low >= top - theta;
       if (done) {
         const int ta = (bk << kBinShift) - 3;         // selected: below ta
         const int tb = ((bk + 1) << kBinShift) + 3;   // not selected: tb and above
@@ -1635,9 +1647,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         for (uint32_t m = amb; m; m &= m - 1) {
           const int k = pos_of(__ffs(m) - 1);
           const int v = pos_v(k);
+          const int slot = atomicAdd(&sBCount, 1);
           const double sc = pos_score(k);
           const uint64_t key = key_of(v);
-          const int slot = atomicAdd(&sBCount, 1);
           if (slot < kBoundaryCap) {
             sBScore[slot] = sc;
             sBKey[slot] = key;
@@ -1681,8 +1693,6 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           btotal = top;
         }
       }
-    } else {
-      if (wave == NW - 1 && more) set_row(P, row ^ 1, dnext);
     }
     if (!done) {
     // ---- top-K and the theta cut, exactly.  A first pass finds the best and the
@@ -1767,15 +1777,15 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       if (bn != 0xFFFFu) atomicAdd(&sHisto[bn], 1u);
     }
     lds_barrier();
-    const int nbinned = find_bin(K);
+    const Found f0 = find_bin(K);
     // the K-th candidate's bin is resolved, or every binned candidate is selected
     int beta0 = kBins, nlev = 1, need = 0, nbc = 0, cntb = 0;
     bool all_bin = false;
-    const bool resolve = nbinned >= K;
+    const bool resolve = f0.bin < kBins;
     if (resolve) {
-      beta0 = sBucket;
-      need = K - sAbove;
-      cntb = sBucketCnt;
+      beta0 = f0.bin;
+      need = K - f0.above;
+      cntb = f0.count;
     }
     // level 0 decides every candidate outside the boundary bin: above it taken,
     // below it dropped; bnd marks this lane's candidates inside it
@@ -1820,6 +1830,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           sLvInv[L] = lv_hi > lv_lo ? static_cast<double>(kBins) / (lv_hi - lv_lo) : 0.0;
           sLvShift[L] = lv_hi > lv_lo ? -1 : (key_shift > 0 ? key_shift : 0);
         }
+        // (block_minmax's barrier follows every wavefront's scan of the bins)
         for (int d = tid; d < kBins; d += BLOCK) sHisto[d] = 0;
         lds_barrier();
         last_shift = sLvShift[L];
@@ -1827,10 +1838,10 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         if (key_level) key_shift -= kBinBits;
         for_bnd(L, [&](int, int v, double sc) { atomicAdd(&sHisto[bin_at(L, v, sc)], 1u); });
         lds_barrier();
-        (void)find_bin(need);
-        if (tid == 0) sLvBeta[L] = sBucket;
-        need -= sAbove;
-        cntb = sBucketCnt;
+        const Found f = find_bin(need);
+        if (tid == 0) sLvBeta[L] = f.bin;
+        need -= f.above;
+        cntb = f.count;
         nlev = L + 1;
         lds_barrier();
       }
@@ -1955,6 +1966,18 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       reinterpret_cast<uint4*>(&N.Lw[r * kMaxSub])[1] = w_L23;
       reinterpret_cast<uint4*>(&N.hist[r * kMaxSub])[0] = w_hist;
     }
+    // the memory that a completed word's scoring reads first, touched here: its
+    // wavefronts then find it in the CU's cache
+    uint32_t t0_ = 0, t1_ = 0, t2_ = 0, t3_ = 0, t4_ = 0, t5_ = 0;
+    if (kAhead && is_event) {
+      const int nsub = (w_meta >> 8) & 0xFF;
+      t0_ = arena[w_hist.x].blk;
+      if (nsub > 1) t1_ = arena[w_hist.y].blk;
+      if (nsub > 2) t2_ = arena[w_hist.z].blk;
+      if (nsub > 3) t3_ = arena[w_hist.w].blk;
+      t4_ = static_cast<uint32_t>(trie_words[w_woff]);
+      t5_ = wrank[w_woff].h;
+    }
     if (wave < RW) {
       const uint64_t evs = __ballot(is_event);
       if (is_event)  // the hypothesis, its sub-beams, the completed word's node
@@ -1962,7 +1985,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
             uint4{static_cast<uint32_t>(r), (w_meta >> 8) & 0xFFu, w_woff, static_cast<uint32_t>(w_tmask >> kWordCountShift)};
       if (lane == 0) sEvCnt[wave] = __popcll(evs);
     }
-    if (!kSplit || wave >= RW) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (the frame before's history nodes)
+    if (wave >= RW) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (the frame before's history nodes)
     lds_barrier();  // the new hypotheses, their keys and the completed words are in place
     mark(kPhNewBeam);
     int nev = 0;
@@ -1971,10 +1994,13 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
 
     // ---- Eq. (1) for the completed words, and, on the wavefronts that hold the
     // hypotheses, the next frame's recombination, which needs none of its
-    // results: neither waits for the other.  (An instance with no wavefront
-    // to spare scores first.)
-    if (!kSplit || (wave >= RW && wave < RW + LMW)) {
-      score_words(P, S, N, nev, kSplit ? wave - RW : wave, LMW, lane);
+    // results: neither waits for the other.  The row after the next one's is set
+    // by the last wavefront, or, if that one may have words to score, by the
+    // first one after its recombination.
+    const bool last_busy = LMW == NW - RW && nev > 4 * (LMW - 1);
+    if (wave == NW - 1 && !last_busy && tau + 2 < tend) set_row(P, row, dnext);
+    if (wave >= RW && wave < RW + LMW) {
+      score_words(P, S, N, nev, wave - RW, LMW, lane);
       // the history nodes (global memory) are read by the fusion, if this frame
       // fuses, else by the next frame's scoring: then they are waited for at
       // the end of its selection
@@ -1987,6 +2013,8 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         N.first[r] = tn.first_child;
         N.woff[r] = tn.word_off;
       }
+      if (wave == 0 && last_busy && tau + 2 < tend) set_row(P, row, load_row(tau + 2, lane));
+      asm volatile("" ::"v"(t0_), "v"(t1_), "v"(t2_), "v"(t3_), "v"(t4_), "v"(t5_));
     }
     {
       // nodes reserved this frame; past the capacity the count stays at cap + 1
@@ -2713,7 +2741,7 @@ hipError_t launch_decode(int K, const KArgs* args, const float* logits, const in
   if (K <= 16 && spare)
     LB_DECODE(16, 16, 1, true, 16, 256);
   else if (K <= 16)
-    LB_DECODE(16, 4, 1, true, 4, 64);
+    LB_DECODE(16, 8, 1, true, 8, 128);
   else if (K <= 32 && spare)
     LB_DECODE(32, 16, 1, true, 16, 512);
   else if (K <= 32)
@@ -2723,7 +2751,7 @@ hipError_t launch_decode(int K, const KArgs* args, const float* logits, const in
   else if (K <= 64 && B > 3 * cus)
     LB_DECODE(64, 4, 4, false, 16, 256);
   else if (K <= 64)
-    LB_DECODE(64, 4, 1, true, 4, 256);
+    LB_DECODE(64, 4, 3, true, 4, 256);
   else if (K <= 128)
     LB_DECODE(128, 4, 1, true, 4, 512);
   else if (spare)
