@@ -541,9 +541,60 @@ struct BeamLds {
 };
 
 template <int NT, int N>
+__device__ __forceinline__ void write_output(const DevParams& P, const DevState& S, int b, const int32_t* lengths,
+                                             int32_t Tc, int32_t fin, int32_t* out_hyps, float* out_scores, int n,
+                                             bool root, double total, uint64_t key, uint32_t hist, double* sc,
+                                             uint64_t* ky, uint32_t* ix, uint32_t* hh, int32_t* sScan);
+template <int NT, int N>
 __device__ __forceinline__ void emit_output(const DevParams& P, const DevState& S, int b, const int32_t* lengths,
                                             int32_t Tc, int32_t fin, int32_t* out_hyps, float* out_scores, double* sc,
-                                            uint64_t* ky, uint32_t* ix, int32_t* sScan);
+                                            uint64_t* ky, uint32_t* ix, uint32_t* hh, int32_t* sScan);
+
+// The best end-of-sentence mark after `word` by the synthetic scorer (the
+// first of equal scores), or -1 without marks.
+__device__ inline int32_t best_eos(const DevParams& P, int32_t word, double* score) {
+  int32_t best = -1;
+  double bs = kNegInf;
+  for (int k = 0; k < P.eos_count; ++k) {
+    const double v = bigram_score(P, word, P.eos_ids[k]);
+    if (v > bs) {
+      bs = v;
+      best = P.eos_ids[k];
+    }
+  }
+  *score = bs;
+  return best;
+}
+
+// The synthetic fusion score of a history at the end of an utterance: its best
+// end-of-sentence mark, where there are marks, counts with it.
+__device__ inline double final_score(const DevParams& P, const HistNode& hn) {
+  double f = hn.sfus;
+  if (P.eos_count > 0) {
+    double e;
+    (void)best_eos(P, hn.word, &e);
+    f += e;
+  }
+  return f;
+}
+
+// Stable sort of nsub sub-beams, the best score first.
+__device__ __forceinline__ void rank_subs(int nsub, double* L, uint32_t* h) {
+#pragma unroll
+  for (int pass = 0; pass < kMaxSub - 1; ++pass) {
+#pragma unroll
+    for (int j = 0; j + 1 < kMaxSub; ++j) {
+      if (j + 1 < nsub && L[j] < L[j + 1]) {
+        const double tL = L[j];
+        L[j] = L[j + 1];
+        L[j + 1] = tL;
+        const uint32_t th = h[j];
+        h[j] = h[j + 1];
+        h[j + 1] = th;
+      }
+    }
+  }
+}
 
 // Frames [tau0, min(tau1, length)) of Alg. 1 for every stream: one workgroup
 // per stream, which keeps the stream's beam in LDS from frame to frame.  Each
@@ -630,7 +681,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   constexpr int FUSE_BYTES = KMAX >= 128 ? 4 * kBins + 24 * KMAX : 20 * KMAX;
   constexpr int MAX1 = SEL_BYTES > LM_BYTES ? SEL_BYTES : LM_BYTES;
   constexpr int UNI_BYTES = MAX1 > FUSE_BYTES ? MAX1 : FUSE_BYTES;
-  static_assert(20 * KMAX <= SEL_BYTES, "output sort scratch");
+  static_assert(24 * KMAX <= UNI_BYTES, "output sort scratch");
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -645,6 +696,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // 1..40, and every symbol's distance from it in units, 65535 at most, in the
   // order in which the lanes own them (word ln * NH + p: slots p and p + NH)
   __shared__ double sDtop[2];
+  __shared__ double sQ[2];  // units per nat, nats per unit
   // the bonus of a class (beta, gamma for the separator; 0 past it): a select
   // between two parameters would be a load from global memory in every lane
   __shared__ double sBonus[64];
@@ -697,14 +749,11 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   uint64_t* const sBKey = reinterpret_cast<uint64_t*>(sSel + kBoundaryCap * 8);
   uint32_t* const sBSrc = reinterpret_cast<uint32_t*>(sSel + kBoundaryCap * 16);
   LmWave* const sLm = reinterpret_cast<LmWave*>(sSel);
-  // the output (when this launch writes it) sorts in the shared scratch
-  auto output = [&](const DevParams& Pr, const DevState& Sr) {
-    emit_output<BLOCK, KMAX>(Pr, Sr, b, lengths, Tc, out_fin, out_hyps, out_scores, reinterpret_cast<double*>(sSel),
-                             reinterpret_cast<uint64_t*>(sSel + 8 * KMAX),
-                             reinterpret_cast<uint32_t*>(sSel + 16 * KMAX), sScan);
-  };
   if (tau0 >= tend) {  // no frames of this stream in the launch
-    if (out_hyps) output(P, S);
+    if (out_hyps)
+      emit_output<BLOCK, KMAX>(P, S, b, lengths, Tc, out_fin, out_hyps, out_scores, reinterpret_cast<double*>(sSel),
+                               reinterpret_cast<uint64_t*>(sSel + 8 * KMAX), reinterpret_cast<uint32_t*>(sSel + 16 * KMAX),
+                               reinterpret_cast<uint32_t*>(sSel + 20 * KMAX), sScan);
     return;
   }
 
@@ -730,28 +779,49 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   const uint32_t arena0 = 1u + static_cast<uint32_t>(static_cast<uint64_t>(b) * S.arena_cap);
 
   // ---- the stream's beam into LDS
+  // (every entry's fields with the number of entries, in one round of reads;
+  // those past it are left)
   int n = S.nbeam[b];
-  if (tid < n) {
+  {
     BeamLds<KMAX>& B0 = sBeam[0];
     const size_t g = gb + tid;
-    B0.key[tid] = S.key[g];
-    B0.pkey[tid] = S.pkey[g];
-    B0.ab[tid] = S.ab[g];
-    B0.anb[tid] = S.anb[g];
-    B0.pt[tid] = S.pt[g];
-    const uint32_t node = S.node[g];
-    const uint32_t meta = S.meta[g];
-    B0.node[tid] = node;
-    B0.meta[tid] = meta;
-    const int nsub = (meta >> 8) & 0xFF;
-    for (int j = 0; j < nsub; ++j) {
-      B0.Lw[tid * kMaxSub + j] = S.Lw[g * O + j];
-      B0.hist[tid * kMaxSub + j] = S.hist[g * O + j];
+    uint64_t key = 0, pkey = 0;
+    double ab = 0.0, anb = 0.0, pt = 0.0, Lw[kMaxSub] = {};
+    uint32_t node = 0, meta = 0, hist[kMaxSub] = {};
+    if (tid < K) {
+      key = S.key[g];
+      pkey = S.pkey[g];
+      ab = S.ab[g];
+      anb = S.anb[g];
+      pt = S.pt[g];
+      node = S.node[g];
+      meta = S.meta[g];
+#pragma unroll
+      for (int j = 0; j < kMaxSub; ++j) {
+        if (j < O) {
+          Lw[j] = S.Lw[g * O + j];
+          hist[j] = S.hist[g * O + j];
+        }
+      }
     }
-    const TrieNode tn = S.trie[node];
-    B0.tmask[tid] = tn.mask;
-    B0.first[tid] = tn.first_child;
-    B0.woff[tid] = tn.word_off;
+    if (tid < n) {
+      const TrieNode tn = trie[node];
+      B0.key[tid] = key;
+      B0.pkey[tid] = pkey;
+      B0.ab[tid] = ab;
+      B0.anb[tid] = anb;
+      B0.pt[tid] = pt;
+      B0.node[tid] = node;
+      B0.meta[tid] = meta;
+#pragma unroll
+      for (int j = 0; j < kMaxSub; ++j) {
+        B0.Lw[tid * kMaxSub + j] = Lw[j];
+        B0.hist[tid * kMaxSub + j] = hist[j];
+      }
+      B0.tmask[tid] = tn.mask;
+      B0.first[tid] = tn.first_child;
+      B0.woff[tid] = tn.word_off;
+    }
   }
   if (tid < 7) sCnt[tid] = 0;
   if (tid < 6) {
@@ -793,10 +863,14 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // units per nat of the 16-bit scores: they reach theta, at most 14, plus 2 nats
   // down from a frame's reference (the K-th candidate lies 2 nats below the best
   // in the middle, 10 in one frame of a hundred)
-  const double qunit = (fmin(P.theta, 14.0) + 2.0) / 65000.0, qscale = 1.0 / qunit;
+  if (tid == 0) {
+    const double unit = (fmin(P.theta, 14.0) + 2.0) / 65000.0;
+    sQ[0] = 1.0 / unit;
+    sQ[1] = unit;
+  }
   // D = alpha * log-probs of a frame into row q of sD, by one wavefront (every
   // lane): raw scores are first normalised by a log-softmax over the 41 classes
-  auto set_row = [&](const DevParams& Pr, int q, float xin) {
+  auto set_row = [&](const DevParams& Pr, int q, float xin, int lane) {
     double x = lane < kClasses ? static_cast<double>(xin) : kNegInf;
     if (Pr.raw_input) {
       double m = x, unused = x;
@@ -811,7 +885,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     const double top = wave_max(sym ? db : kNegInf);
     if (lane == 0) sDtop[q] = top;
     if (sym) {
-      const double u = (top - db) * qscale;
+      const double u = (top - db) * sQ[0];
       const int ln = (lane - 1) / NC, k = (lane - 1) % NC;
       const int h = 2 * (ln * NH + (k < NH ? k : k - NH)) + (k < NH ? 0 : 1);
       reinterpret_cast<uint16_t*>(&sDq[q][0])[h] = u < 65535.0 ? static_cast<uint16_t>(u) : uint16_t{65535};  // (also of NaN)
@@ -825,8 +899,8 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     return lane < kClasses && t < tend ? logits[(static_cast<size_t>(b) * Tc + t) * kClasses + lane] : 0.0f;
   };
   lds_barrier();
-  if (wave == 0) set_row(P, 0, load_row(tau0, lane));
-  if (wave == 1) set_row(P, 1, load_row(tau0 + 1, lane));
+  if (wave == 0) set_row(P, 0, load_row(tau0, lane), lane);
+  if (wave == 1) set_row(P, 1, load_row(tau0 + 1, lane), lane);
   float dnext = 0.0f;
   lds_barrier();
   // the loaded hypotheses' keys for the first frame, and their best total
@@ -1560,7 +1634,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     bool done = false;
 
     // ---- top-K by 16-bit scores: a candidate's distance below a reference, in
-    // units of 1 / qscale nat, as the sum of its hypothesis' and its symbol's,
+    // units of sQ[1] nats, as the sum of its hypothesis' and its symbol's,
     // both rounded down -- two slots in one saturating packed addition, where
     // the 64-bit score and its bin took a dozen instructions per slot and first
     // needed the range of the scores, a reduction over the workgroup.  (With
@@ -1587,6 +1661,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     if (done) {
       typedef unsigned short us2 __attribute__((ext_vector_type(2)));
       constexpr int NP = NH + 1;  // the pairs of slots, and (stay, repeat)
+      const double qscale = sQ[0];
       const double p = C.pt[hi_], lw = C.Lw[hi_ * kMaxSub], dtop = sDtop[row];
       const double sc_s = sPt2[hi_] + lw;
       const double sc_r = ((C.ab[hi_] + Dc[last_]) + sBonus[last_]) + lw;
@@ -1616,6 +1691,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         }
       }
       lds_barrier();
+      const double qunit = sQ[1];
       const Found f = find_bin(K);
       const int bk = f.bin;
       // no candidate scores above top, the K-th at least low
@@ -1998,7 +2074,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     // by the last wavefront, or, if that one may have words to score, by the
     // first one after its recombination.
     const bool last_busy = LMW == NW - RW && nev > 4 * (LMW - 1);
-    if (wave == NW - 1 && !last_busy && tau + 2 < tend) set_row(P, row, dnext);
+    if (wave == NW - 1 && !last_busy && tau + 2 < tend) set_row(P, row, dnext, lane);
     if (wave >= RW && wave < RW + LMW) {
       score_words(P, S, N, nev, wave - RW, LMW, lane);
       // the history nodes (global memory) are read by the fusion, if this frame
@@ -2013,7 +2089,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         N.first[r] = tn.first_child;
         N.woff[r] = tn.word_off;
       }
-      if (wave == 0 && last_busy && tau + 2 < tend) set_row(P, row, load_row(tau + 2, lane));
+      if (wave == 0 && last_busy && tau + 2 < tend) set_row(P, row, load_row(tau + 2, lane), lane);
       asm volatile("" ::"v"(t0_), "v"(t1_), "v"(t2_), "v"(t3_), "v"(t4_), "v"(t5_));
     }
     {
@@ -2171,21 +2247,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
             h[j] = 0;
           }
         }
-        // stable bubble sort, descending
-#pragma unroll
-        for (int pass = 0; pass < kMaxSub - 1; ++pass) {
-#pragma unroll
-          for (int j = 0; j + 1 < kMaxSub; ++j) {
-            if (j + 1 < nsub && L[j] < L[j + 1]) {
-              const double tL = L[j];
-              L[j] = L[j + 1];
-              L[j + 1] = tL;
-              const uint32_t th = h[j];
-              h[j] = h[j + 1];
-              h[j + 1] = th;
-            }
-          }
-        }
+        rank_subs(nsub, L, h);
 #pragma unroll
         for (int j = 0; j < kMaxSub; ++j) {
           if (j < nsub) {
@@ -2205,21 +2267,63 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     if constexpr (DB) cur ^= 1;
   }
 
-  // ---- the beam back to HBM
+  // (the thread index opaque again: addresses of the load above are not kept
+  // through the frames for the write-back)
   {
-    const BeamLds<KMAX>& E = sBeam[DB ? cur : 0];
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const size_t gb = static_cast<size_t>(b) * K;
+  // ---- the end of an utterance: the final fusion of every hypothesis
+  BeamLds<KMAX>& E = sBeam[DB ? cur : 0];
+  if (out_hyps && out_fin && fuse_frames) {
     if (tid < n) {
-      const size_t g = gb + tid;
-      S.key[g] = E.key[tid];
-      S.pkey[g] = E.pkey[tid];
-      S.ab[g] = E.ab[tid];
-      S.anb[g] = E.anb[tid];
-      S.pt[g] = E.pt[tid];
-      S.node[g] = E.node[tid];
-      const uint32_t meta = E.meta[tid];
-      S.meta[g] = meta;
-      const int nsub = (meta >> 8) & 0xFF;
-      for (int j = 0; j < nsub; ++j) {
+      const int nsub = (E.meta[tid] >> 8) & 0xFF;
+      double L[kMaxSub];
+      uint32_t h[kMaxSub];
+#pragma unroll
+      for (int j = 0; j < kMaxSub; ++j) {
+        L[j] = kNegInf;
+        h[j] = 0;
+        if (j < nsub) {
+          h[j] = E.hist[tid * kMaxSub + j];
+          L[j] = P.phi * final_score(P, arena[h[j]]);
+        }
+      }
+      rank_subs(nsub, L, h);
+#pragma unroll
+      for (int j = 0; j < kMaxSub; ++j) {
+        if (j < nsub) {
+          E.Lw[tid * kMaxSub + j] = L[j];
+          E.hist[tid * kMaxSub + j] = h[j];
+        }
+      }
+    }
+    if (tid == 0) sCnt[5] += static_cast<unsigned long long>(n);
+  }
+
+  // ---- the beam back to HBM (each thread the entry that it fused)
+  bool o_root = false;
+  double o_total = kNegInf;
+  uint64_t o_key = ~0ull;
+  uint32_t o_hist = 0;
+  if (tid < n) {
+    const size_t g = gb + tid;
+    o_key = E.key[tid];
+    o_root = E.node[tid] == kRootNode;
+    o_total = E.pt[tid] + E.Lw[tid * kMaxSub];
+    o_hist = E.hist[tid * kMaxSub];
+    S.key[g] = o_key;
+    S.pkey[g] = E.pkey[tid];
+    S.ab[g] = E.ab[tid];
+    S.anb[g] = E.anb[tid];
+    S.pt[g] = E.pt[tid];
+    S.node[g] = E.node[tid];
+    const uint32_t meta = E.meta[tid];
+    S.meta[g] = meta;
+    const int nsub = (meta >> 8) & 0xFF;
+#pragma unroll
+    for (int j = 0; j < kMaxSub; ++j) {
+      if (j < nsub) {
         S.Lw[g * O + j] = E.Lw[tid * kMaxSub + j];
         S.hist[g * O + j] = E.hist[tid * kMaxSub + j];
       }
@@ -2239,23 +2343,26 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     atomicAdd(&sCnt[2], static_cast<unsigned long long>(c_queries));
     atomicAdd(&sCnt[3], static_cast<unsigned long long>(plines));
   }
-  __syncthreads();
+  lds_barrier();
   if (tid == 0) {
     S.nbeam[b] = n;
     S.arena_n[b] = arena_n;
+    // (this workgroup's own counters: the additions are atomic so that nothing waits for their old values)
     unsigned long long* cn = S.counters + static_cast<size_t>(b) * kNumCounters;
-    cn[kCntExpansions] += sCnt[4];
-    cn[kCntFrames] += static_cast<unsigned long long>(tend - tau0);
-    cn[kCntWordEvents] += sCnt[1];
-    cn[kCntLmQueries] += sCnt[2];
-    cn[kCntFused] += sCnt[5];
-    cn[kCntProbeLines] += sCnt[0] + sCnt[3];
-    cn[kCntPresLines] += sCnt[3];
-    cn[kCntLookups] += sCnt[6];
+    atomicAdd(&cn[kCntExpansions], sCnt[4]);
+    atomicAdd(&cn[kCntFrames], static_cast<unsigned long long>(tend - tau0));
+    atomicAdd(&cn[kCntWordEvents], sCnt[1]);
+    atomicAdd(&cn[kCntLmQueries], sCnt[2]);
+    atomicAdd(&cn[kCntFused], sCnt[5]);
+    atomicAdd(&cn[kCntProbeLines], sCnt[0] + sCnt[3]);
+    atomicAdd(&cn[kCntPresLines], sCnt[3]);
+    atomicAdd(&cn[kCntLookups], sCnt[6]);
   }
-  if (out_hyps) {
-    __syncthreads();  // the beam is back in global memory
-    output(P, S);
+  if (out_hyps)
+    write_output<BLOCK, KMAX>(P, S, b, lengths, Tc, out_fin, out_hyps, out_scores, n, o_root, o_total, o_key, o_hist,
+                              reinterpret_cast<double*>(sSel), reinterpret_cast<uint64_t*>(sSel + 8 * KMAX),
+                              reinterpret_cast<uint32_t*>(sSel + 16 * KMAX), reinterpret_cast<uint32_t*>(sSel + 20 * KMAX),
+                              sScan);
   }
   if (timing) {
     __syncthreads();
@@ -2301,29 +2408,11 @@ __device__ __forceinline__ void select_fused(const DevParams& P, const DevState&
 }
 
 // Delayed fusion on the selected hypotheses of stream b (Eq. (2)): each
-// sub-beam's word-level score becomes phi * its fusion score -- the synthetic
-// score kept in its history node, or the caller's ext[b][rank][j] -- and the
+// sub-beam's word-level score becomes phi * its fusion score -- the caller's
+// ext[b][rank][j], or the synthetic score at the end of an utterance -- and the
 // sub-beams are re-ranked (stable).
-// The best end-of-sentence mark after `word` by the synthetic scorer (the
-// first of equal scores), or -1 without marks.
-__device__ inline int32_t best_eos(const DevParams& P, int32_t word, double* score) {
-  int32_t best = -1;
-  double bs = kNegInf;
-  for (int k = 0; k < P.eos_count; ++k) {
-    const double v = bigram_score(P, word, P.eos_ids[k]);
-    if (v > bs) {
-      bs = v;
-      best = P.eos_ids[k];
-    }
-  }
-  *score = bs;
-  return best;
-}
-
-// With `eos` (the final synthetic fusion) each sub-beam's fusion score also
-// takes its best end-of-sentence mark.
 template <int BLOCK>
-__device__ __forceinline__ void apply_fused(const DevParams& P, const DevState& S, int b, const float* ext, bool eos = false) {
+__device__ __forceinline__ void apply_fused(const DevParams& P, const DevState& S, int b, const float* ext) {
   const int tid = threadIdx.x;
   const size_t gb = static_cast<size_t>(b) * P.K;
   const int F = S.fsel_n[b];
@@ -2341,13 +2430,7 @@ __device__ __forceinline__ void apply_fused(const DevParams& P, const DevState& 
         if (ext) {
           f = static_cast<double>(ext[(gb + tid) * P.O + j]);
         } else {
-          const HistNode hn = S.arena[h[j]];
-          f = hn.sfus;
-          if (eos) {
-            double e;
-            (void)best_eos(P, hn.word, &e);
-            f += e;
-          }
+          f = final_score(P, S.arena[h[j]]);
         }
         L[j] = P.phi * f;
       } else {
@@ -2355,21 +2438,7 @@ __device__ __forceinline__ void apply_fused(const DevParams& P, const DevState& 
         h[j] = 0;
       }
     }
-    // stable bubble sort, descending
-#pragma unroll
-    for (int pass = 0; pass < kMaxSub - 1; ++pass) {
-#pragma unroll
-      for (int j = 0; j + 1 < kMaxSub; ++j) {
-        if (j + 1 < nsub && L[j] < L[j + 1]) {
-          const double tL = L[j];
-          L[j] = L[j + 1];
-          L[j + 1] = tL;
-          const uint32_t th = h[j];
-          h[j] = h[j + 1];
-          h[j + 1] = th;
-        }
-      }
-    }
+    rank_subs(nsub, L, h);
 #pragma unroll
     for (int j = 0; j < kMaxSub; ++j) {
       if (j < nsub) {
@@ -2498,38 +2567,30 @@ __global__ __launch_bounds__(BLOCK) void k_fuse_apply(const DevParams P, const D
 
 // ------------------------------------------------------------------ output
 
-// One stream's output: at the end of an utterance the final synthetic fusion
-// over all hypotheses and the mid-word filter (when some hypothesis ends at a
-// word boundary); then the hypotheses ranked by
-// (total desc, key asc), each one's words traced back from its best sub-beam,
-// rows padded with -1.  Run by a whole workgroup of NT threads; the sort covers
-// N >= K entries (N a power of two, N <= NT) in sc / ky / ix; sScan holds
-// NT / 64 entries.
+// One stream's output: at the end of an utterance the mid-word filter (when some
+// hypothesis ends at a word boundary); then the hypotheses ranked by (total
+// desc, key asc), each one's words traced back from its best sub-beam, rows
+// padded with -1.  Run by a whole workgroup of NT threads; thread i < n holds
+// hypothesis i (root: it ends at a word boundary; hist: its best sub-beam's
+// history).  The sort covers N >= K entries (N a power of two, N <= NT) in sc /
+// ky / ix; hh holds N histories, sScan NT / 64 entries.
 template <int NT, int N>
-__device__ __forceinline__ void emit_output(const DevParams& P, const DevState& S, int b, const int32_t* lengths,
-                                            int32_t Tc, int32_t fin, int32_t* out_hyps, float* out_scores, double* sc,
-                                            uint64_t* ky, uint32_t* ix, int32_t* sScan) {
+__device__ __forceinline__ void write_output(const DevParams& P, const DevState& S, int b, const int32_t* lengths,
+                                             int32_t Tc, int32_t fin, int32_t* out_hyps, float* out_scores, int n,
+                                             bool root, double total, uint64_t key, uint32_t hist, double* sc,
+                                             uint64_t* ky, uint32_t* ix, uint32_t* hh, int32_t* sScan) {
   const int tid = threadIdx.x;
-  if (fin && P.fusion_source == 1 && P.fusion_interval > 0) {
-    select_fused<N>(P, S, b, 0, sc, ky, ix);
-    apply_fused<N>(P, S, b, nullptr, P.eos_count > 0);
-  }
-  const int n = S.nbeam[b];
-  const size_t gb = static_cast<size_t>(b) * P.K;
   // at the end of an utterance, hypotheses inside a word are dropped when at
   // least one hypothesis ends at a word boundary; otherwise all are ranked
   int nroot = 0;
-  bool root = false;
-  if (fin) {
-    root = tid < n && S.node[gb + tid] == kRootNode;
-    (void)block_scan<NT>(root ? 1 : 0, sScan, &nroot);
-  }
+  if (fin) (void)block_scan<NT>(tid < n && root ? 1 : 0, sScan, &nroot);
   bool ok = false;
   if (tid < n) {
     ok = !fin || root || nroot == 0;
-    sc[tid] = ok ? S.pt[gb + tid] + S.Lw[(gb + tid) * P.O] : kNegInf;
-    ky[tid] = ok ? S.key[gb + tid] : ~0ull;
+    sc[tid] = ok ? total : kNegInf;
+    ky[tid] = ok ? key : ~0ull;
     ix[tid] = tid;
+    hh[tid] = hist;
   } else if (tid < N) {
     sc[tid] = kNegInf;
     ky[tid] = ~0ull;
@@ -2576,9 +2637,8 @@ __device__ __forceinline__ void emit_output(const DevParams& P, const DevState& 
     int32_t* row = out_hyps + (static_cast<size_t>(b) * P.K + r) * P.W;
     int n = 0;
     if (r < m) {
-      const size_t bi = gb + ix[r];
       out_scores[static_cast<size_t>(b) * P.K + r] = static_cast<float>(sc[r]);
-      const uint32_t h = S.hist[bi * P.O];
+      const uint32_t h = hh[ix[r]];
       const HistNode top = S.arena[h];
       const int len = static_cast<int>(top.depth);
       // at the end of an utterance with end-of-sentence marks, the best mark follows the words
@@ -2600,6 +2660,32 @@ __device__ __forceinline__ void emit_output(const DevParams& P, const DevState& 
   pad_rows<NT>(out_hyps + static_cast<size_t>(b) * P.K * P.W, P.K, P.W, sLen);
 }
 
+// The output of a stream's beam in global memory, at the end of an utterance
+// after the final synthetic fusion over all hypotheses.
+template <int NT, int N>
+__device__ __forceinline__ void emit_output(const DevParams& P, const DevState& S, int b, const int32_t* lengths,
+                                            int32_t Tc, int32_t fin, int32_t* out_hyps, float* out_scores, double* sc,
+                                            uint64_t* ky, uint32_t* ix, uint32_t* hh, int32_t* sScan) {
+  const int tid = threadIdx.x;
+  if (fin && P.fusion_source == 1 && P.fusion_interval > 0) {
+    select_fused<N>(P, S, b, 0, sc, ky, ix);
+    apply_fused<N>(P, S, b, nullptr);
+  }
+  const int n = S.nbeam[b];
+  const size_t i = static_cast<size_t>(b) * P.K + tid;
+  bool root = false;
+  double total = kNegInf;
+  uint64_t key = ~0ull;
+  uint32_t hist = 0;
+  if (tid < n) {
+    root = S.node[i] == kRootNode;
+    total = S.pt[i] + S.Lw[i * P.O];
+    key = S.key[i];
+    hist = S.hist[i * P.O];
+  }
+  write_output<NT, N>(P, S, b, lengths, Tc, fin, out_hyps, out_scores, n, root, total, key, hist, sc, ky, ix, hh, sScan);
+}
+
 // The output as a launch of its own (when the call's last decode launch did
 // not write it).
 template <int BLOCK>
@@ -2609,9 +2695,9 @@ __global__ __launch_bounds__(BLOCK) void k_output(const DevParams P, const DevSt
                                                   float* __restrict__ out_scores) {
   __shared__ double sc[BLOCK];
   __shared__ uint64_t ky[BLOCK];
-  __shared__ uint32_t ix[BLOCK];
+  __shared__ uint32_t ix[BLOCK], hh[BLOCK];
   __shared__ int32_t sScan[BLOCK / 64];
-  emit_output<BLOCK, BLOCK>(P, S, blockIdx.x, lengths, Tc, fin, out_hyps, out_scores, sc, ky, ix, sScan);
+  emit_output<BLOCK, BLOCK>(P, S, blockIdx.x, lengths, Tc, fin, out_hyps, out_scores, sc, ky, ix, hh, sScan);
 }
 
 // ------------------------------------------------------------------ gather ceiling
