@@ -2598,27 +2598,31 @@ __device__ __forceinline__ void write_output(const DevParams& P, const DevState&
   }
   int m = 0;
   (void)block_scan<NT>(ok ? 1 : 0, sScan, &m);
-  if constexpr (N <= 64) {
-    // up to 64 entries: each one's position is the number of entries before
-    // it in (score desc, key asc, index asc), counted by one wavefront (two
-    // barriers instead of the sort's stages)
-    double si = kNegInf;
-    uint64_t ki = ~0ull;
+  // lanes per entry: the position of an entry is the number of those before it in
+  // (score desc, key asc, index asc), counted by NT / N lanes, a share each (two
+  // barriers; a sort of 256 entries takes 36 barrier-separated stages, and one
+  // lane per entry took 3 us for 64); without lanes to share, from 128 entries
+  // on, a sort
+  constexpr int LANES = NT / N;
+  if constexpr (LANES > 1 || N <= 64) {
+    static_assert(LANES <= 16 && (LANES & (LANES - 1)) == 0, "an entry's lanes are neighbours in a wavefront");
+    const int i = tid / LANES, part = tid % LANES;  // (NT == N * LANES)
+    const double si = sc[i];
+    const uint64_t ki = ky[i];
     int rk = 0;
-    if (tid < N) {
-      si = sc[tid];
-      ki = ky[tid];
-      for (int j = 0; j < N; ++j) {
-        const double sj = sc[j];
-        const uint64_t kj = ky[j];
-        rk += (ranks_before(sj, kj, si, ki) || (sj == si && kj == ki && j < tid)) ? 1 : 0;
-      }
+#pragma unroll 8
+    for (int j = part; j < N; j += LANES) {
+      const double sj = sc[j];
+      const uint64_t kj = ky[j];
+      rk += (ranks_before(sj, kj, si, ki) || (sj == si && kj == ki && j < i)) ? 1 : 0;
     }
+#pragma unroll
+    for (int o = 1; o < LANES; o <<= 1) rk += __shfl_xor(rk, o, 64);
     __syncthreads();
-    if (tid < N) {
+    if (part == 0) {
       sc[rk] = si;
       ky[rk] = ki;
-      ix[rk] = static_cast<uint32_t>(tid);
+      ix[rk] = static_cast<uint32_t>(i);
     }
   } else {
     bitonic_sort<N>(sc, ky, ix);
@@ -2629,7 +2633,7 @@ __device__ __forceinline__ void write_output(const DevParams& P, const DevState&
     const int32_t len = lengths[b];
     const int32_t adv = len < 0 ? 0 : (len > Tc ? Tc : len);
     if (adv != len) atomicOr(S.flags, kFlagLength);
-    S.t0[b] += adv;
+    atomicAdd(reinterpret_cast<unsigned long long*>(&S.t0[b]), static_cast<unsigned long long>(adv));
   }
   int32_t* const sLen = reinterpret_cast<int32_t*>(ky);  // words written per rank (the keys are read)
   __syncthreads();
