@@ -667,8 +667,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // score completed words meanwhile: the others, as many as a beam can fill
   constexpr int RW = (KMAX + 63) / 64;
   constexpr int kWordWaves = (KMAX + kWaveWords - 1) / kWaveWords;
-  constexpr int LMW = NW - RW < kWordWaves ? NW - RW : kWordWaves;
-  static_assert(NW > RW, "a wavefront to score words");
+  // (a block of one wavefront scores them before the recombination)
+  constexpr int LM0 = NW > RW ? RW : 0;
+  constexpr int LMW = NW - LM0 < kWordWaves ? NW - LM0 : kWordWaves;
   // score bins of the top-K selection: 1024 at K = 256; 512 for the smaller
   // beams' fewer candidates (c5: 25.69 against 25.83 ms with 1024; c4 9.91
   // against 9.80 with 512)
@@ -738,7 +739,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // scores words (taken after the barrier that ends the phase, or, inside Eq.
   // (1), where that wavefront is done with it)
   auto mark = [&](int k) {
-    if (timing && threadIdx.x == 64 * RW) {
+    if (timing && threadIdx.x == 64 * LM0) {
       const unsigned long long now = __builtin_amdgcn_s_memtime();
       sPhase[k] += now - sPhase[kPhases];
       sPhase[kPhases] = now;
@@ -900,7 +901,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   };
   lds_barrier();
   if (wave == 0) set_row(P, 0, load_row(tau0, lane), lane);
-  if (wave == 1) set_row(P, 1, load_row(tau0 + 1, lane), lane);
+  if (wave == NW - 1) set_row(P, 1, load_row(tau0 + 1, lane), lane);
   float dnext = 0.0f;
   lds_barrier();
   // the loaded hypotheses' keys for the first frame, and their best total
@@ -2061,7 +2062,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
             uint4{static_cast<uint32_t>(r), (w_meta >> 8) & 0xFFu, w_woff, static_cast<uint32_t>(w_tmask >> kWordCountShift)};
       if (lane == 0) sEvCnt[wave] = __popcll(evs);
     }
-    if (wave >= RW) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (the frame before's history nodes)
+    if (wave >= LM0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (the frame before's history nodes)
     lds_barrier();  // the new hypotheses, their keys and the completed words are in place
     mark(kPhNewBeam);
     int nev = 0;
@@ -2073,10 +2074,10 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     // results: neither waits for the other.  The row after the next one's is set
     // by the last wavefront, or, if that one may have words to score, by the
     // first one after its recombination.
-    const bool last_busy = LMW == NW - RW && nev > 4 * (LMW - 1);
+    const bool last_busy = LMW == NW - LM0 && nev > 4 * (LMW - 1);
     if (wave == NW - 1 && !last_busy && tau + 2 < tend) set_row(P, row, dnext, lane);
-    if (wave >= RW && wave < RW + LMW) {
-      score_words(P, S, N, nev, wave - RW, LMW, lane);
+    if (wave >= LM0 && wave < LM0 + LMW) {
+      score_words(P, S, N, nev, wave - LM0, LMW, lane);
       // the history nodes (global memory) are read by the fusion, if this frame
       // fuses, else by the next frame's scoring: then they are waited for at
       // the end of its selection
@@ -2813,13 +2814,22 @@ hipError_t launch_decode(int K, const KArgs* args, const float* logits, const in
                          uint32_t opts, void* scratch, hipStream_t st) {
   unsigned char* const scr = static_cast<unsigned char*>(scratch);
   const KArgs LB_CONST* A = (const KArgs LB_CONST*)args;
-  // One workgroup per stream.  A batch that leaves CUs to spare gets more
-  // lanes per hypothesis (up to 512 threads per stream, LPB <= 16); a batch
-  // with more streams than one round of workgroups holds gets the instances
-  // that fit more workgroups per CU: K = 64 with 4 per CU instead of 3 (128
-  // registers, some spilling; one in-place LDS beam buffer), K = 256 with 2 per
-  // CU (one in-place LDS beam buffer; two lanes per hypothesis, 512 threads,
-  // so 128 registers).
+  // One workgroup per stream; a frame is a chain of latencies, so the instances
+  // trade lanes and registers per stream against workgroups per CU.
+  // - A batch that leaves CUs to spare: 256 or 512 threads per stream (four times
+  //   as many lanes per hypothesis at K <= 32, twice at K = 64, as many wavefronts
+  //   for the words as a beam can fill), registers without a limit.
+  // - More streams than CUs: the instances that fit more workgroups per CU.
+  //   K <= 16: 128 threads, 6 per CU; past that one wavefront per stream in 128
+  //   registers, 12 to 13 per CU (60 frames at K = 16, 1536 streams: 0.537 ms
+  //   against 0.451 with 128 threads; 2000: 0.534 against 0.752; 3072: 0.571
+  //   against 1.014).
+  //   K <= 32: 128 threads, 6 per CU.
+  //   K <= 64: 256 threads, 3 per CU; past that 4 in 128 registers with the beam
+  //   in place.
+  //   K <= 128 and K <= 256: 512 threads, 2 per CU in 128 registers with the beam
+  //   in place (one per CU, 512 streams x 200 frames at K = 100: 2.841 ms; two:
+  //   1.575.  At K = 128 with 10 M n-grams, 700 x 100: 2.546 and 1.762).
   const int cus = cu_count();
   const bool spare = B <= cus;
   // (hash slots per hypothesis: 16 with one workgroup per CU and K <= 64, 8 at
@@ -2830,6 +2840,8 @@ hipError_t launch_decode(int K, const KArgs* args, const float* logits, const in
             fin, out_hyps, out_scores, opts, scr)
   if (K <= 16 && spare)
     LB_DECODE(16, 16, 1, true, 16, 256);
+  else if (K <= 16 && B > 6 * cus)
+    LB_DECODE(16, 4, 4, false, 4, 64);
   else if (K <= 16)
     LB_DECODE(16, 8, 1, true, 8, 128);
   else if (K <= 32 && spare)
@@ -2842,6 +2854,8 @@ hipError_t launch_decode(int K, const KArgs* args, const float* logits, const in
     LB_DECODE(64, 4, 4, false, 16, 256);
   else if (K <= 64)
     LB_DECODE(64, 4, 3, true, 4, 256);
+  else if (K <= 128 && !spare)
+    LB_DECODE(128, 4, 4, false, 8, 512);
   else if (K <= 128)
     LB_DECODE(128, 4, 1, true, 4, 512);
   else if (spare)

@@ -411,7 +411,7 @@ SELECTION_CASES = {
 }
 
 
-@pytest.mark.parametrize("beam,big", [(8, 300), (32, 300), (64, 800), (128, 0), (256, 300)])
+@pytest.mark.parametrize("beam,big", [(8, 300), (12, 1700), (32, 300), (64, 800), (128, 300), (256, 300)])
 @pytest.mark.parametrize("case", sorted(SELECTION_CASES))
 def test_selection_by_coarse_scores(case, beam, big):
     """The top-K's 16-bit scores at their limits and past them, in every launch
@@ -452,7 +452,7 @@ def test_selection_by_coarse_scores(case, beam, big):
 
 
 @pytest.mark.parametrize("heavy", [0, -1])
-@pytest.mark.parametrize("beam,big", [(16, 300), (64, 800), (100, 0), (256, 300)])
+@pytest.mark.parametrize("beam,big", [(16, 300), (16, 1700), (64, 800), (100, 300), (256, 300)])
 def test_many_words_completed_per_frame(beam, big, heavy):
     """A lexicon of one-phoneme spellings with 1, 2, 3, 18 or 40 homophones and
     nearly flat frames, so that a good part of the beam completes words in
