@@ -623,9 +623,9 @@ __device__ __forceinline__ void rank_subs(int nsub, double* L, uint32_t* h) {
 // After the last frame the beam goes back to global memory, and, when out_hyps
 // is given, the workgroup also writes the stream's output (emit_output; out_fin:
 // the end of the utterance).
-// Barriers per frame: the histogram, the bin search, the boundary's list, the
-// gather, the new hypotheses (two when in place), and the one that joins Eq. (1)
-// and the next recombination (the exact selection, where it is needed, has more).
+// Barriers per frame: the histogram, the boundary's list, the selection, the new
+// hypotheses (two when in place), and the one that joins Eq. (1) and the next
+// recombination (the exact selection, where it is needed, has more).
 // WPE: wavefronts per SIMD the register allocation aims for (four workgroups
 // of 256 threads per CU need 4).  DB: the hypotheses are double-buffered in
 // LDS; otherwise one buffer is rewritten in place (every source entry is read
@@ -633,7 +633,7 @@ __device__ __forceinline__ void rank_subs(int nsub, double* L, uint32_t* h) {
 // CU.  HSF: LDS hash slots per hypothesis for the prefix keys (more slots,
 // shorter linear probe chains, more LDS).  The decoder's parameters and state
 // (P, S) are read from their device copy A_ in constant memory.  opts bit 0
-// (kOptPhaseTimers): thread 0 adds the clock cycles of each phase of the
+// (kOptPhaseTimers): one thread adds the clock cycles of each phase of the
 // frame to the stream's phase counters (kCntPhase0 + kPh*).  scratch: when
 // given, the n-gram lookup scratch of the call's streams (scratch_layout)
 // instead of the decoder's own buffers.
@@ -670,9 +670,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   // (a block of one wavefront scores them before the recombination)
   constexpr int LM0 = NW > RW ? RW : 0;
   constexpr int LMW = NW - LM0 < kWordWaves ? NW - LM0 : kWordWaves;
-  // score bins of the top-K selection: 1024 at K = 256; 512 for the smaller
-  // beams' fewer candidates (c5: 25.69 against 25.83 ms with 1024; c4 9.91
-  // against 9.80 with 512)
+  // score bins of the top-K selection: 512 from K = 128 on; 256 for the smaller
+  // beams' fewer candidates (512 x 500 frames at K = 256: 5.39 ms with 512, 5.54
+  // with 256; 256 x 500 at K = 64: 3.21 with 256, 3.25 with 512)
   constexpr int kBinBits = KMAX >= 128 ? 9 : 8;
   constexpr int kBins = 1 << kBinBits;
   constexpr int kBinShift = 16 - kBinBits;  // of a 16-bit score
@@ -1561,7 +1561,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     const int hi_ = tid / LPB;
     const int ln = tid - hi_ * LPB;
     const bool live = hi_ < n;
-    const int last_ = static_cast<int>(C.meta[hi_] & 0xFF);
+    const int last_ = static_cast<int>(C.meta[hi_] & 0x3F);  // (a class; in range also of what lies past the last hypothesis)
     // bit k: slot k is an extension (the trie mask is cut to bits 1..40, its
     // bits 48..63 hold the node's word count)
     uint32_t c_val = static_cast<uint32_t>((C.tmask[hi_] & ~sCut[hi_] & ((2ull << kSep) - 1ull)) >> (1 + NC * ln)) & ((1u << NC) - 1u);
@@ -2077,6 +2077,10 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     const bool last_busy = LMW == NW - LM0 && nev > 4 * (LMW - 1);
     if (wave == NW - 1 && !last_busy && tau + 2 < tend) set_row(P, row, dnext, lane);
     if (wave >= LM0 && wave < LM0 + LMW) {
+      // (a chain of dependent reads that the others wait for at the next barrier:
+      // it issues first.  512 x 500 frames at K = 256 5.30 -> 5.15 ms, 1024
+      // streams in ten calls at K = 64 1.72 -> 1.69, fewer per CU unchanged.)
+      __builtin_amdgcn_s_setprio(2);
       score_words(P, S, N, nev, wave - LM0, LMW, lane);
       // the history nodes (global memory) are read by the fusion, if this frame
       // fuses, else by the next frame's scoring: then they are waited for at
