@@ -2372,7 +2372,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   if (timing) {
     __syncthreads();
     mark(kPhOther);
-    if (tid == 0) {
+    if (threadIdx.x == 64 * LM0) {  // (the thread that marks: it alone knows the last interval)
       unsigned long long* cn = S.counters + static_cast<size_t>(b) * kNumCounters;
       for (int k = 0; k < kPhases; ++k) cn[kCntPhase0 + k] += sPhase[k];
     }

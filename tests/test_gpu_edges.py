@@ -314,7 +314,9 @@ def test_profiling_changes_nothing_and_leaves_no_error(name):
     st, H, S = dec.decode(torch.from_numpy(d.logits).to(dev), torch.from_numpy(d.lengths.astype(np.int32)).to(dev))
     torch.cuda.synchronize()
     s = lbm.lb_get_stats(dec.handle)
-    assert all(int(c) > 0 for c in s.phase_cycles[:3]), list(s.phase_cycles)
+    # (one counter per phase: recombination, top-K, new beam, grouping, lookups, ranking, fusion, the rest)
+    assert s.word_events > 0 and s.fused > 0
+    assert all(int(c) > 0 for c in s.phase_cycles), list(s.phase_cycles)
     assert s.timed[lbm.KIND_DECODE] == 1 and s.timed[lbm.KIND_BEGIN] == 1
     dec.close()
     x = torch.ones(1 << 20, device=dev).sum()  # raises if a HIP error was left behind
@@ -325,6 +327,32 @@ def test_profiling_changes_nothing_and_leaves_no_error(name):
     for b in range(B):
         n = len(plain[b][0])
         assert np.array_equal(Sn[b, :n], plain[b][1])
+
+
+@pytest.mark.parametrize("beam", [8, 64, 256])
+def test_phase_counters_hold_the_output(beam):
+    """The last phase counter takes what follows the frames in: with output rows
+    of 4 MiB to pad it grows, against rows of 16 words, by at least the cycles
+    that one compute unit takes to store them (64 B a cycle; half of that is
+    asked for)."""
+    import torch
+    d = load_workload("t-c1k", batch=1)
+    dev = torch.device("cuda:0")
+    last = []
+    for W in (16, (1 << 20) // beam):
+        say(f"[case] phase counters K={beam} W={W}")
+        lp = lbm.make_params(DecodeParams(**{**d.workload.params.__dict__, "beam": beam}), max_batch=1, max_frames=4)
+        lp.max_words_out = W
+        dec = lbm.Decoder(d.lexicon, d.lm, lp)
+        lbm.lb_set_profiling(dec.handle, lbm.LB_PROFILE_PHASES)
+        st, _, _ = dec.decode(torch.from_numpy(d.logits[:1, :4].copy()).to(dev),
+                              torch.tensor([4], dtype=torch.int32, device=dev))
+        assert st == lbm.LB_OK
+        torch.cuda.synchronize()
+        last.append(int(dec.stats().phase_cycles[7]))
+        dec.close()
+    say(f"[case] phase counters K={beam}: {last}")
+    assert last[1] - last[0] > (4 << 20) / 128, last
 
 
 # ------------------------------------------------------------------ gather ceiling probe
