@@ -1245,6 +1245,10 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
                           (static_cast<double>(c.bo2) + (static_cast<double>(c.bo1) + static_cast<double>(logp)));
         return lw + comega * lp;
       };
+      // A candidate put at an empty list's head without a comparison: a score that
+      // is no number (omega = 0 times a log10 P of -inf) counts as -inf there, as no
+      // comparison would ever move it.  (insert leaves such a candidate out.)
+      auto head = [&](double L) -> double { return fmax(L, kNegInf); };
       // the word's k-th homophone in unigram order
       auto ranked = [&](uint32_t k) -> WordRank {
         auto pick = [&](uint32_t a, uint32_t b, uint32_t c, uint32_t d) -> uint32_t {
@@ -1259,7 +1263,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         const int nl = static_cast<int>(gc & ~kGroupHeavy);
         // (the first candidate of an empty list is put there)
         if (nl > 0) {
-          tL[0] = Lw + comega * res_lp(off);
+          tL[0] = head(Lw + comega * res_lp(off));
           tq[0] = (j << 16) | static_cast<int>(walk ? E[0] : 0u);
           ts[0] = off;
         }
@@ -1275,7 +1279,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           uint32_t k = 0;
           if (nl == 0) {
             const WordRank wr = ranked(0);
-            tL[0] = unigram_score(ctx, Lw, wr.logp);
+            tL[0] = head(unigram_score(ctx, Lw, wr.logp));
             tq[0] = (j << 16) | static_cast<int>(wr.h);
             ts[0] = -1;
             got = 1;

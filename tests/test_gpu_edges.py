@@ -513,6 +513,57 @@ def test_many_words_completed_per_frame(beam, big, heavy):
             assert wide[b][0] == out[b % B][0] and np.array_equal(wide[b][1], out[b % B][1]), b
 
 
+def same_as_oracle(out, d, p, orc, lengths):
+    """Every rank's words and its score (32-bit rounding of the oracle's): for
+    decisions at exact ties, which check_parity would excuse."""
+    import oracle
+    op = oracle.params_from(p, fusion_seed=d.fusion_seed)
+    for b in range(len(lengths)):
+        r = orc.decode(d.logits[b, :lengths[b]], op)
+        assert [list(w) for w in out[b][0]] == [[int(x) for x in w] for w in r.words], b
+        assert np.allclose(out[b][1], np.array(r.total), rtol=1e-6, atol=1e-4), b
+
+
+@pytest.mark.parametrize("omega", [0.0, 0.5])
+@pytest.mark.parametrize("heavy", [0, -1])
+@pytest.mark.parametrize("beam,big", [(8, 1700), (64, 800), (256, 300)])
+def test_homophones_without_a_score(beam, big, heavy, omega):
+    """Spellings some of whose 2 to 40 homophones have no score (no unigram in
+    an LM without <unk>, or an explicit -inf): first or last among them, or all
+    but one.  At omega = 0 their score is 0 x -inf.  The output is the oracle's
+    for the lexicon without them."""
+    import oracle
+    words, scored = [], []
+    for ph in range(1, 21):
+        n = (2, 2, 3, 5, 18, 40)[ph % 6]
+        words += [(ph,)] * n
+        scored += ([False] + [True] * (n - 1), [True] * (n - 1) + [False], [False] * (n - 1) + [True])[ph % 3]
+    W = len(words)
+    good = [w for w in range(W) if scored[w]]
+    rng = np.random.default_rng(17)
+    uni = [((w,), -float(rng.uniform(1, 4)), -float(rng.uniform(0, 1))) for w in good + [W]]
+    uni += [((w,), -np.inf, 0.0) for w in range(0, W, 2) if not scored[w]]
+    pairs = sorted({(int(rng.choice(good)), int(rng.choice(good))) for _ in range(300)})
+    lm = lm_from_entries(W, [uni, [(g, -float(rng.uniform(0.5, 3)), 0.0) for g in pairs], [], []])
+    lex = lexicon_from(words)
+    known = lexicon_from([words[w] for w in good])
+    known.entry_word = np.array(good, np.int32)
+    T, lengths = 16, [16, 13, 16]
+    lg = np.stack([peaked_logits([int(x) for x in rng.integers(0, 41, size=T)], strong=0.5, seed=80 + b, sigma=0.7)
+                   for b in range(3)])
+    p = DecodeParams(beam=beam, subbeams=3, omega=omega, fusion_interval=5, fusion_top_f=beam // 2)
+    d = data_of(lex, lm, lg, p, fusion_seed=4, lengths=lengths)
+    say(f"[case] homophones without a score K={beam} heavy={heavy} omega={omega}")
+    out = gpu_decode(d, params=p, lb_overrides=dict(heavy_homophones=heavy))
+    same_as_oracle(out, d, p, oracle.Oracle(known, lm), lengths)
+    tile = lambda a: np.concatenate([a] * (big // 3 + 1))[:big]
+    db = data_of(lex, lm, tile(lg), p, fusion_seed=4, lengths=tile(d.lengths))
+    say(f"[case] homophones without a score K={beam} heavy={heavy} omega={omega} B={big}")
+    wide = gpu_decode(db, params=p, lb_overrides=dict(heavy_homophones=heavy))
+    for b in range(big):
+        assert wide[b][0] == out[b % 3][0] and np.array_equal(wide[b][1], out[b % 3][1]), b
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_random_small_lexicons_match_oracle(seed):
     """Random small lexicons over phonemes 1..5 (one to four phonemes a word,
