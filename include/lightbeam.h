@@ -198,7 +198,10 @@ void lb_destroy(lb_decoder* dec);
  *               their completed words)
  *   out_hyps    device int32 [batch][beam][max_words_out]: word ids of the best
  *               sub-beam of each ranked hypothesis, -1 padded
- *   out_scores  device float32 [batch][beam]: total scores, -inf padded
+ *   out_scores  device float32 [batch][beam]: total scores, -inf padded (a
+ *               hypothesis whose last word has no score in any reading -- no
+ *               unigram and an LM without <unk> -- has a total of -inf, and its
+ *               words, until the next frame drops it or a fusion scores it)
  * Hypothesis state persists across calls (streaming).  Without LB_END the
  * outputs rank the current hypotheses (completed words only).  With
  * LB_FUSION_EXTERNAL the call may return LB_NEED_FUSION: the caller then calls

@@ -515,6 +515,7 @@ constexpr int kWaveTasks = 16;
 constexpr uint32_t kTopWords = 4;  // of a heavy word, read ahead in unigram order (o + 1 decide it, o <= 3)
 constexpr int kLmRes = 64;
 constexpr uint32_t kLaneMaxH = 16;
+constexpr int kNoCandidate = 0x7FFFFFFF;  // an empty place of a ranked list (after every sub-beam << 16 | homophone)
 struct LmWave {
   double lp[kLmRes];
   QState st[kLmRes];
@@ -1221,7 +1222,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
 #pragma unroll
       for (int k = 0; k < kMaxSub; ++k) {
         tL[k] = kNegInf;
-        tq[k] = 0x7FFFFFFF;
+        tq[k] = kNoCandidate;
         ts[k] = 0;
       }
       auto insert = [&](double L, int qq, int ss) {
@@ -1303,7 +1304,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
         }
       }
       // o rounds of an arg-max over the word's four lanes; lane k keeps the k-th
-      // winner; lambda is relative to the best
+      // winner; lambda is relative to the best.  A word whose every reading scores
+      // -inf keeps them: its hypothesis is never a candidate again, unless a fusion
+      // scores it anew, but it has sub-beams and their histories, as every one has
       double myL = kNegInf, bestL = kNegInf;
       int myq = 0, mys = 0, kept = 0;
       bool open = true;
@@ -1313,15 +1316,15 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           // the best head; of equal ones the first in (sub-beam, homophone) order
           double m4 = fmax(tL[0], dpp_f64<kDppXor1>(tL[0], kNegInf));
           m4 = fmax(m4, dpp_f64<kDppXor2>(m4, kNegInf));
-          int q4 = tL[0] == m4 ? tq[0] : 0x7FFFFFFF;
-          q4 = min(q4, dpp_i32<kDppXor1>(q4, 0x7FFFFFFF));
-          q4 = min(q4, dpp_i32<kDppXor2>(q4, 0x7FFFFFFF));
+          int q4 = tL[0] == m4 ? tq[0] : kNoCandidate;
+          q4 = min(q4, dpp_i32<kDppXor1>(q4, kNoCandidate));
+          q4 = min(q4, dpp_i32<kDppXor2>(q4, kNoCandidate));
           const bool win = tL[0] == m4 && tq[0] == q4;
           int s4 = win ? ts[0] : 0;
           s4 |= dpp_i32<kDppXor1>(s4, 0);
           s4 |= dpp_i32<kDppXor2>(s4, 0);
           if (k == 0) bestL = m4;
-          open = open && m4 != kNegInf && !(m4 < bestL - lam);
+          open = open && q4 != kNoCandidate && !(m4 < bestL - lam);
           if (open) {
             if (j == k) {
               myL = m4;
@@ -1338,7 +1341,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
               ts[m] = ts[m + 1];
             }
             tL[kMaxSub - 1] = kNegInf;
-            tq[kMaxSub - 1] = 0x7FFFFFFF;
+            tq[kMaxSub - 1] = kNoCandidate;
           }
         }
       }
@@ -1355,7 +1358,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
 #pragma unroll
         for (int k = 0; k < kMaxSub; ++k) {
           sL[k] = kNegInf;
-          sq[k] = 0x7FFFFFFF;
+          sq[k] = kNoCandidate;
           ss[k] = 0;
         }
         auto put = [&](double L, int qq, int sr) {
@@ -1379,7 +1382,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           const uint32_t xc = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(gc), l0 + jj));
           const int xo = __builtin_amdgcn_readlane(off, l0 + jj);
           if (!(xc & kGroupHeavy)) {
-            for (int h = lane; h < xH; h += 64) put(lw + comega * res_lp(xo + h), (jj << 16) | h, xo + h);
+            for (int h = lane; h < xH; h += 64) put(head(lw + comega * res_lp(xo + h)), (jj << 16) | h, xo + h);
           } else {
             // lane m holds the m-th listed homophone, a candidate with its
             // looked-up score; the others in unigram order, 64 at a time, until
@@ -1389,7 +1392,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
             uint32_t eh = kNone;
             if (lane < ne) {
               eh = scrE[static_cast<size_t>(e0 * kMaxSub + xl) * kMaxExplicit + lane];
-              put(lw + comega * res_lp(xo + lane), (jj << 16) | static_cast<int>(eh), xo + lane);
+              put(head(lw + comega * res_lp(xo + lane)), (jj << 16) | static_cast<int>(eh), xo + lane);
             }
             Ctx cx{};
             cx.bo1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ctx.bo1), l0 + jj));
@@ -1408,7 +1411,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
                 member |= static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(eh), m)) == wr.h;
               const double L = unigram_score(cx, lw, wr.logp);
               const bool cand = valid && !member;
-              if (cand) put(L, (jj << 16) | static_cast<int>(wr.h), -1 - k);
+              if (cand) put(head(L), (jj << 16) | static_cast<int>(wr.h), -1 - k);
               const double lastL = readlane_f64(L, last);
               cum += __popcll(__ballot(cand && L > lastL));
               if (cum >= O) break;
@@ -1423,7 +1426,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
           double bL = sL[0];
           int bq = sq[0];
           wave_argmax(&bL, &bq);
-          if (bL == kNegInf) break;
+          if (bq == kNoCandidate) break;
           if (k == 0) xbest = bL;
           if (bL < xbest - lam) break;
           const bool holder = sL[0] == bL && sq[0] == bq;  // one lane: queries are distinct
@@ -1442,7 +1445,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
               ss[m] = ss[m + 1];
             }
             sL[kMaxSub - 1] = kNegInf;
-            sq[kMaxSub - 1] = 0x7FFFFFFF;
+            sq[kMaxSub - 1] = kNoCandidate;
           }
           xkept = k + 1;
         }
@@ -1648,7 +1651,8 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     // 500 frames at K = 256 7.39 -> 5.86 ms, 256 x 500 at K = 64 4.17 -> 3.62.)
     // The distance is at
     // most 2 units above the 16-bit score (and less than one more for the
-    // rounding of the 64-bit sums, all below 1e9 here).  So with the K-th
+    // rounding of the 64-bit sums, all below 1e9 here: a lower word-level score,
+    // or one of -inf, puts its candidates past the 16 bits).  So with the K-th
     // candidate in bin b of 2^kBinShift units, every candidate 3 units before
     // the bin is selected, none 3 units past it is, and those between, ranked
     // exactly by (score desc, key asc), fill the rest.
@@ -1676,7 +1680,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
       for (int w = 0; w < NH; ++w) q2[w] = __builtin_bit_cast(us2, sDq[row][ln * NH + w]);
       auto units = [&](double sc) -> uint32_t { return static_cast<uint32_t>(fmin(fmax((ref - sc) * qscale, 0.0), 65535.0)); };
       const uint32_t bq = units(base), qs = units(sc_s), qr = units(sc_r);
-      const bool wild = !(fabs(p) < 1e9 && fabs(lw) < 1e9 && base <= ref) || (stays && !(sc_s <= ref)) || (reps && !(sc_r <= ref));
+      const bool wild = !(fabs(p) < 1e9 && lw < 1e9 && base <= ref) || (stays && !(sc_s <= ref)) || (reps && !(sc_r <= ref));
       if (live && wild) sWild = tau + 1;
       const us2 b2 = __builtin_bit_cast(us2, bq | (bq << 16));
 #pragma unroll

@@ -564,6 +564,60 @@ def test_homophones_without_a_score(beam, big, heavy, omega):
         assert wide[b][0] == out[b % 3][0] and np.array_equal(wide[b][1], out[b % 3][1]), b
 
 
+@pytest.mark.parametrize("omega,interval", [(0.0, 0), (0.5, 0), (0.5, 5)])
+@pytest.mark.parametrize("beam,big", [(8, 1700), (64, 800), (256, 300)])
+def test_spellings_without_a_scored_word(beam, big, interval, omega):
+    """Spellings none of whose 1 to 40 words has a score: the word's total is
+    -inf, its hypothesis ends there unless a fusion scores it again, and its
+    words are those of the best sub-beam all the same.  One call, calls of 1 and
+    3 frames (the hypothesis lies in memory between them) and a tiled batch, at
+    the end and live: the oracle's ranks, those of -inf among them.  (At
+    omega = 0 the score is 0 x -inf; the oracle's omega is then so small that
+    it moves no total.)"""
+    import oracle
+    import torch
+    words, scored = [], []
+    for ph in range(1, 21):
+        n = (1, 2, 3, 5, 40)[ph % 5]
+        words += [(ph,)] * n
+        scored += [ph % 4 != 0] * n
+    W = len(words)
+    uni = [((w,), -1.0, 0.0) for w in range(W) if scored[w]] + [((W,), -1.0, 0.0)]
+    lex, lm = lexicon_from(words), lm_from_entries(W, [uni, [], [], []])
+    rng = np.random.default_rng(23)
+    T, lengths = 14, [14, 11, 14]
+    lg = np.stack([peaked_logits([int(x) for x in rng.integers(0, 41, size=T)], strong=0.5, seed=90 + b, sigma=0.7)
+                   for b in range(3)])
+    p = DecodeParams(beam=beam, subbeams=3, omega=omega, fusion_interval=interval, fusion_top_f=beam // 2)
+    d = data_of(lex, lm, lg, p, fusion_seed=6, lengths=lengths)
+    orc = oracle.Oracle(lex, lm)
+    dead = 0
+    for fin in (True, False):
+        op = oracle.params_from(p, fusion_seed=6, finalize=int(fin), omega=omega or 1e-300)
+        ref = [orc.decode(lg[b, :lengths[b]], op) for b in range(3)]
+        dead += sum(int(np.isneginf(r.total).sum()) for r in ref)
+        for B, chunk in ((3, T), (3, 1), (3, 3), (big, T)):
+            say(f"[case] spellings without a score K={beam} I={interval} omega={omega} end={fin} B={B} chunk={chunk}")
+            tile = [b % 3 for b in range(B)]
+            dec = lbm.Decoder(lex, lm, lbm.make_params(p, max_batch=B, max_frames=T, fusion_seed=6))
+            for lo in range(0, T, chunk):
+                part = torch.from_numpy(np.ascontiguousarray(lg[tile, lo:lo + chunk])).cuda()
+                ln = torch.from_numpy(np.clip(d.lengths[tile] - lo, 0, part.shape[1]).astype(np.int32)).cuda()
+                flags = (lbm.LB_BEGIN if lo == 0 else 0) | (lbm.LB_END if fin and lo + chunk >= T else 0)
+                st, H, S = dec.decode(part, ln, flags)
+                assert st == lbm.LB_OK
+            assert dec.status() == lbm.LB_OK
+            H, S = H.cpu().numpy(), S.cpu().numpy()
+            dec.close()
+            for b in range(B):
+                r = ref[b % 3]
+                n = len(r.words)
+                assert [[int(x) for x in row[row >= 0]] for row in H[b, :n]] == [[int(x) for x in w] for w in r.words], b
+                assert np.allclose(S[b, :n], r.total, rtol=0, atol=1e-4), b
+                assert (H[b, n:] == -1).all() and np.isneginf(S[b, n:]).all(), b
+    assert interval or dead > 0  # (a fusion scores every hypothesis at the end)
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_random_small_lexicons_match_oracle(seed):
     """Random small lexicons over phonemes 1..5 (one to four phonemes a word,
