@@ -610,6 +610,13 @@ lb_status lb_create(const lb_lexicon_desc* lex, const lb_ngram_desc* lm, const l
   P.seed = p.fusion_seed;
   P.lo = p.fusion_lo;
   P.hi = p.fusion_hi;
+  // the 16-bit scores reach theta, at most 14, plus 2 nats down from a frame's
+  // reference (the K-th candidate lies 2 nats below the best in the middle, 10 in
+  // one frame of a hundred).  A bonus of 1e9 or more may cancel a score as large,
+  // and what the 64-bit sums round away then is more than they allow for
+  const double unit = (std::min(p.theta, 14.0) + 2.0) / 65000.0;
+  P.qscale = 1.0 / unit;
+  P.qunit = std::fabs(p.beta) < 1e9 && std::fabs(p.gamma) < 1e9 ? unit : std::nan("");
   {
     const KArgs ka{P, S};
     hipError_t e = hipSuccess;

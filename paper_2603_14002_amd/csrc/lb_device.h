@@ -162,6 +162,8 @@ struct DevParams {
   double alpha, beta, gamma, comega, phi, theta, lam;
   uint64_t seed;
   double lo, hi;
+  // the top-K's 16-bit scores: units per nat, nats per unit (NaN: they are not to be trusted)
+  double qscale, qunit;
 };
 
 struct DevState {

@@ -862,13 +862,9 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
   uint32_t* const scrE = (scratch ? reinterpret_cast<uint32_t*>(scratch + slay.off_explicit) : S.scrE) +
                          static_cast<size_t>(b) * P.K * kMaxSub * kMaxExplicit;
   if (tid < 64) sBonus[tid] = tid >= 1 && tid < kSep ? P.beta : (tid == kSep ? P.gamma : 0.0);
-  // units per nat of the 16-bit scores: they reach theta, at most 14, plus 2 nats
-  // down from a frame's reference (the K-th candidate lies 2 nats below the best
-  // in the middle, 10 in one frame of a hundred)
   if (tid == 0) {
-    const double unit = (fmin(P.theta, 14.0) + 2.0) / 65000.0;
-    sQ[0] = 1.0 / unit;
-    sQ[1] = unit;
+    sQ[0] = P.qscale;
+    sQ[1] = P.qunit;
   }
   // D = alpha * log-probs of a frame into row q of sD, by one wavefront (every
   // lane): raw scores are first normalised by a log-softmax over the 41 classes
@@ -1659,7 +1655,7 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     // The reference bounds every candidate from above: the beam's best total
     // plus the best that this frame can add (its blank, or its best symbol with
     // its bonus, and log 3 for the paths that a stay sums).  Where it does not
-    // (a word raised a hypothesis; scores of 1e9), where fewer than K candidates
+    // (a word raised a hypothesis; scores or bonuses of 1e9), where fewer than K candidates
     // are within the 16 bits, where theta may cut or the bin is crowded, the
     // exact selection below takes the frame.
     double ref = 0.0;

@@ -524,6 +524,31 @@ def same_as_oracle(out, d, p, orc, lengths):
         assert np.allclose(out[b][1], np.array(r.total), rtol=1e-6, atol=1e-4), b
 
 
+@pytest.mark.parametrize("beam,big", [(4, 1700), (32, 300), (64, 800), (256, 300)])
+def test_selection_with_bonuses_that_cancel(beam, big):
+    """Bonuses of 2^54 against symbols of -2^54: every extension's total is
+    rounded to a multiple of 4, which the 16-bit scores, summed in another
+    order, cannot see.  The exact selection's beams (exact ties by key)."""
+    import oracle
+    rng = np.random.default_rng(31)
+    words = sorted({tuple(int(x) for x in rng.integers(1, 7, size=int(rng.integers(1, 4)))) for _ in range(60)})
+    lex, lm = lexicon_from(words), random_small_lm(len(words), 400)
+    T, lengths = 24, [24, 19, 24]
+    lg = np.full((3, T, 41), -2.0 ** 54, np.float32)
+    lg[:, :, 0] = rng.uniform(-3.0, 0.0, size=(3, T))
+    p = DecodeParams(beam=beam, subbeams=2, alpha=1.0, beta=2.0 ** 54, gamma=2.0 ** 54)
+    d = data_of(lex, lm, lg, p, lengths=lengths)
+    say(f"[case] cancelled bonuses K={beam}")
+    out = gpu_decode(d, params=p)
+    same_as_oracle(out, d, p, oracle.Oracle(lex, lm), lengths)
+    tile = lambda a: np.concatenate([a] * (big // 3 + 1))[:big]
+    db = data_of(lex, lm, tile(lg), p, lengths=tile(d.lengths))
+    say(f"[case] cancelled bonuses K={beam} B={big}")
+    wide = gpu_decode(db, params=p)
+    for b in range(big):
+        assert wide[b][0] == out[b % 3][0] and np.array_equal(wide[b][1], out[b % 3][1]), b
+
+
 @pytest.mark.parametrize("omega", [0.0, 0.5])
 @pytest.mark.parametrize("heavy", [0, -1])
 @pytest.mark.parametrize("beam,big", [(8, 1700), (64, 800), (256, 300)])
