@@ -14,7 +14,6 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
-#include <type_traits>
 
 #include "lb_device.h"
 #include "lb_launch.h"
@@ -141,19 +140,6 @@ __device__ __forceinline__ void wave_argmax(double* L, int* q) {
   }
   *L = bL;
   *q = bq;
-}
-
-template <int BLOCK>
-__device__ inline double block_max(double v, double* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  lds_barrier();
-  double r = red[0];
-#pragma unroll
-  for (int k = 1; k < BLOCK / 64; ++k) r = fmax(r, red[k]);
-  lds_barrier();
-  return r;
 }
 
 // Block-wide maximum of `mx` and minimum of `mn` in one reduction (SYNC as in
