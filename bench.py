@@ -151,8 +151,8 @@ def algorithmic_bytes(s, B, T, p, lp):
     node per 41 expansions, the beam state read and written once per call
     (it stays in LDS between frames), a 64-B line per probed hash-table bucket
     (n-gram tables and continuation index) and per lookup the 64-B line of the
-    word's unigram entry (the queries of a stream-frame that share context
-    and word are looked up once; homophones that back off to their unigram are
+    word's unigram entry (the queries of a completed word's sub-beams that share
+    a context are looked up once; homophones that back off to their unigram are
     not looked up), an 8-B history-node reference per completed word and
     sub-beam, 8 B per fused sub-beam, and, when the decode launch also writes
     the call's output (no separate output launch), the output rows: B x K x
@@ -392,14 +392,15 @@ def main():
         roof["frac_of_copy"] = roof["achieved"] / roof["copy_GBps"]
         # (3) the same K steps with the decode kernel's phase counters on: each
         # phase's share of the workgroups' cycles, and the n-gram lookup phase
-        # against the HBM roofline (its bytes over its share of the launch)
+        # (continuation index and n-gram tables) against the HBM roofline (its
+        # bytes over its share of the launch)
         _, sph = timed_pass(lbm.LB_PROFILE_PHASES)
         cyc = [float(x) for x in sph.phase_cycles]
         tot = sum(cyc)
         if tot > 0:
             share = {n: c / tot for n, c in zip(lbm.PHASE_NAMES, cyc)}
             nl3 = max(1, int(sph.launches[i]))
-            look_bytes = ((sph.probe_lines - sph.index_lines) * LINE_BYTES + sph.lm_lookups * LINE_BYTES) / nl3
+            look_bytes = (sph.probe_lines + sph.lm_lookups) * LINE_BYTES / nl3
             look_s = share["ngram_lookup"] * avg_us * 1e-6
             ach = look_bytes / look_s / 1e9 if look_s > 0 else None
             out_phase = dict(share=share, cycles_per_stream_frame={n: c / max(1, sph.frames) for n, c in
@@ -415,12 +416,15 @@ def main():
                 gather_ceiling=ceil,
                 frac_of_gather_ceiling=None if ach is None else ach / ceil["GBps"],
                 traffic=None, bytes_per_launch=look_bytes,
-                lines_per_launch=(sph.probe_lines - sph.index_lines) / nl3,
+                lines_per_launch=sph.probe_lines / nl3,
+                index_lines_per_launch=sph.index_lines / nl3,
                 lookups_per_launch=sph.lm_lookups / nl3,
                 phase_seconds_per_launch=look_s,
-                timing="the phase's share of the workgroups' clock cycles (s_memtime at its barriers) x the "
-                       "event-timed k_decode launch duration; bytes: a 64-B line per probed bucket of the "
-                       "n-gram tables and per lookup the unigram entry's line")
+                timing="the phase's share of the workgroups' clock cycles (s_memtime around it in one of the "
+                       "wavefronts that score words, beside the next frame's recombination: no barrier "
+                       "closes it) x the event-timed k_decode launch duration; bytes: a 64-B line per probed "
+                       "bucket of the continuation index and the n-gram tables, and per lookup the unigram "
+                       "entry's line")
         else:
             out_phase, roof_lookup = None, None
     out = {
