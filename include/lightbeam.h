@@ -166,8 +166,8 @@ typedef struct lb_stats {
                            launches' workgroups, summed over streams, by phase,
                            as a wavefront that scores words sees them: [0] the
                            part of the next frame's recombination that the
-                           scoring does not cover, and the bin range, [1] top-K
-                           and theta, [2] new beam, [3] grouping of the n-gram
+                           scoring does not cover, [1] top-K and theta, [2] new
+                           beam, [3] grouping of the n-gram
                            queries, [4] continuation index and n-gram lookups,
                            [5] ranking of the completed words (top-o, lambda) and
                            history nodes, [6] fusion (0 without fusion frames),

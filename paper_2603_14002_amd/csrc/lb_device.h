@@ -59,8 +59,8 @@ constexpr uint32_t kFlagLength = 128u;  // a decode call's length outside 0..fra
 
 // phases of a decode frame timed by the phase counters, as the first wavefront
 // that scores completed words sees them: what the next frame's recombination
-// (other wavefronts, at the same time) takes longer than the scoring, and the
-// bin range; top-K selection; new beam; grouping of the n-gram queries; the
+// (other wavefronts, at the same time) takes longer than the scoring; top-K
+// selection; new beam; grouping of the n-gram queries; the
 // lookups (continuation index and n-grams); ranking of the completed words and
 // history nodes; fusion; kPhOther: beam load, write-back and output outside the
 // frame loop

@@ -1529,10 +1529,14 @@ __global__ __launch_bounds__(KMAX * LPB) __attribute__((amdgpu_waves_per_eu(WPE)
     for (int s = tid; s < HS; s += BLOCK) sHKey[s] = kEmptyKey;  // for the new hypotheses' keys
     // Workgroups that share a CU: the CU's arbitration favours the older
     // wavefronts, so the workgroup dispatched second (the later half of the
-    // grid, when workgroups are dispatched to the CUs in order) fell behind
-    // (c4: 9.8 against 11.1 ms on average) and the launch waited for it.  It
-    // gets the higher issue priority in 3 frames of 4, the first one in the
-    // 4th (c4: 12.3 -> 11.7 ms; alternating 1:1 gave 12.1).
+    // grid, when workgroups are dispatched to the CUs in order) falls behind
+    // and the launch waits for it.  It gets the higher issue priority in 3
+    // frames of 4, the first one in the 4th (512 x 500 frames at K = 256: 5.21
+    // ms against 5.46 without; 5.16 against 5.26 with turns 1:1; 1024 streams in
+    // ten calls at K = 64 the same within 0.2 %).  This holds up to the word
+    // scoring: its wavefronts then go to 2 and stay there until their next
+    // frame starts, through a fusion and, in the instance of one wavefront,
+    // through the recombination.
     if ((blockIdx.x >= gridDim.x / 2) ? (tau & 3) != 0 : (tau & 3) == 0)
       __builtin_amdgcn_s_setprio(1);
     else
@@ -2815,15 +2819,27 @@ hipError_t launch_decode(int K, const KArgs* args, const float* logits, const in
   //   for the words as a beam can fill), registers without a limit.
   // - More streams than CUs: the instances that fit more workgroups per CU.
   //   K <= 16: 128 threads, 6 per CU; past that one wavefront per stream in 128
-  //   registers, 12 to 13 per CU (60 frames at K = 16, 1536 streams: 0.537 ms
-  //   against 0.451 with 128 threads; 2000: 0.534 against 0.752; 3072: 0.571
-  //   against 1.014).
-  //   K <= 32: 128 threads, 6 per CU.
+  //   registers, 12 to 13 per CU.
+  //   K <= 32: 128 threads, 6 per CU, past that in two rounds.
   //   K <= 64: 256 threads, 3 per CU; past that 4 in 128 registers with the beam
   //   in place.
   //   K <= 128 and K <= 256: 512 threads, 2 per CU in 128 registers with the beam
-  //   in place (one per CU, 512 streams x 200 frames at K = 100: 2.841 ms; two:
-  //   1.575.  At K = 128 with 10 M n-grams, 700 x 100: 2.546 and 1.762).
+  //   in place.
+  // Both instances at each line, 60 frames, 125k words and 10 M n-grams, us of a
+  // call with 256 streams (256 CUs: the first instance is taken) and with 320 (the
+  // second):
+  //   K <=  16: 256 threads 540, 435; 128 threads 536, 433 (equal)
+  //   K <=  32: 512 threads 627, 785; 128 threads 885, 583
+  //   K <=  64: 512 threads 571, 866; 256 threads 670, 565
+  //   K <= 128: one per CU  621, 1003; two        611, 615
+  //   K <= 256: one per CU  825, 1320; two        828, 851
+  // and past the first one:
+  //   K <= 64, 768 / 800 / 1024 streams: 3 per CU 784, 882, 992; 4 786, 663, 652
+  //   K <= 16, 1536 / 1600 / 2000: 128 threads 621, 696, 918; one wavefront 722,
+  //   771, 804 (60 frames of 20k words, 1536 / 2000 / 3072: 451, 752, 1014 and
+  //   537, 534, 571)
+  //   K <= 32, 1536 / 1600 / 2000: 128 threads 803, 1006, 1143; one wavefront of
+  //   two lanes per hypothesis (no instance of its own) 885, 1089, 1071
   const int cus = cu_count();
   const bool spare = B <= cus;
   // (hash slots per hypothesis: 16 with one workgroup per CU and K <= 64, 8 at

@@ -361,9 +361,9 @@ def test_phase_counters_hold_the_output(beam):
 def test_k256_theta_cut_matches_oracle(theta):
     """A theta small enough to bind inside the beam-256 selection (the cut's
     bin tested exactly against best - theta), in the instance for small
-    batches (two lanes per hypothesis) and the one for batches beyond the CU
-    count (one lane per hypothesis): the oracle's beams, and every copy of a
-    tiled batch decoded like the original."""
+    batches (two beam buffers) and the one for batches beyond the CU count (the
+    beam in place): the oracle's beams, and every copy of a tiled batch decoded
+    like the original."""
     d = load_workload("t-k256")
     p = DecodeParams(**{**d.workload.params.__dict__, "theta": theta})
     n = d.logits.shape[0]
